@@ -13,6 +13,13 @@ constexpr int kMaxDgaussBound = 15;
 // that a kernel reads or writes once.
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+// The same with the alignment of their elements: global memory takes 16-byte
+// accesses at any 4-byte address (8- and 4-byte ones at any element), so rows
+// whose pitch is not a multiple of 16 bytes move as wide as the others.
+typedef f32x4 f32x4_any __attribute__((aligned(4)));
+typedef u32x4 u32x4_any __attribute__((aligned(4)));
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(2)));
+typedef uint32_t u32_any __attribute__((aligned(1)));
 
 // Parameters of one random stream as the kernels see them (passed by value).
 struct RngArgs {
@@ -147,6 +154,25 @@ __device__ __forceinline__ void sample4_aligned(const RngArgs& r, uint64_t e0, u
     out[3] = sparse_from_words(r, b.z, b.w);
   } else {
     out[0] = out[1] = out[2] = out[3] = 0u;
+  }
+}
+
+// Elements e0 .. e0+3 of a SPARSE matrix, e0 any: words 2 e0 .. 2 e0 + 7 lie in
+// two blocks where e0 is even, in three where it is odd.
+__device__ __forceinline__ void sparse4_any(const RngArgs& r, uint64_t e0, uint32_t out[4]) {
+  const uint64_t b = e0 >> 1;
+  const uint4 p = philox_block(r, b), q = philox_block(r, b + 1);
+  if ((e0 & 1) == 0) {
+    out[0] = sparse_from_words(r, p.x, p.y);
+    out[1] = sparse_from_words(r, p.z, p.w);
+    out[2] = sparse_from_words(r, q.x, q.y);
+    out[3] = sparse_from_words(r, q.z, q.w);
+  } else {
+    const uint4 t = philox_block(r, b + 2);
+    out[0] = sparse_from_words(r, p.z, p.w);
+    out[1] = sparse_from_words(r, q.x, q.y);
+    out[2] = sparse_from_words(r, q.z, q.w);
+    out[3] = sparse_from_words(r, t.x, t.y);
   }
 }
 

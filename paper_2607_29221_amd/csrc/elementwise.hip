@@ -129,51 +129,132 @@ __global__ __launch_bounds__(256) void mask_kernel(MaskLaunch a, int64_t groups)
   }
 }
 
-// Fast path of the mask pass for rows of a multiple of 4 columns with
-// contiguous plaintext: four consecutive lanes share one 16-column digit
-// group, lane q owning columns 4q .. 4q+3. A lane reads 4 plaintext values,
-// one 16-byte word of u and one Philox block of noise, and forms the four
-// digit words of its columns; a transpose across the four lanes (quad
-// shuffles) then hands lane q digit plane q of the whole group, so each lane
-// stores 16 contiguous bytes and a wave stores 1 KiB contiguous per
+// The mask pass over contiguous rows: four consecutive lanes share one
+// 16-column digit group, lane q owning columns 4q .. 4q+3. A lane reads 4
+// plaintext values, one 16-byte word of u and one Philox block of noise, and
+// forms the four digit words of its columns; a transpose across the four
+// lanes (quad shuffles) then hands lane q digit plane q of the whole group, so
+// each lane stores 16 contiguous bytes and a wave stores 1 KiB contiguous per
 // instruction. Every input is read once and every output written once, so
 // all accesses are non-temporal (they do not displace cached data).
-// XT: 0 none, 1 int8, 2 int32 or ring words. F: which of u, noise, out and
-// digits are present (MQ_* bits). Presence is a compile-time choice: with
-// run-time tests the loads of x and u were issued one round trip apart.
+// XT: 0 none, 1 int8, 2 int32 or ring words, 3 int16. F: which of u, noise,
+// out and digits are present (MQ_* bits). Presence is a compile-time choice:
+// with run-time tests the loads of x and u were issued one round trip apart.
+//
+// RAGGED: rows of any length at any element address (a row length, pitch or
+// base that is not a multiple of 4 elements), and int16. The loads and stores
+// keep their width at element alignment; only the row's last, partial lane
+// goes element by element. A row's first noise element then sits at word
+// s = (row cols) % 4 of a Philox block, the same s for the whole workgroup
+// (one row each): every lane draws one block and takes its neighbour's through
+// LDS, and only the last wave draws one more, so the draws grow by a quarter
+// where two blocks a lane would double them. The general kernel below, one
+// thread per 16 columns with 4-byte accesses 64 bytes apart and one Philox
+// block per element, took 39 us for 1000 x 5003 codes with u and noise (60 MB,
+// 1.5 TB/s).
 enum { MQ_U = 1, MQ_NOISE = 2, MQ_OUT = 4, MQ_DIG = 8 };
 // Workgroup b covers 1024-column slice b % slices of row b / slices, so
 // consecutive workgroups stream consecutive memory (79% of the HBM peak
 // measured for the int8 mask pass, against 67% with rows varying fastest).
-template <int XT, int F>
+template <int XT, int F, bool RAGGED>
 __global__ __launch_bounds__(256) void mask_quad_kernel(MaskLaunch a, int64_t lanes_per_row, uint32_t slices) {
+  static_assert(XT != 3 || RAGGED, "int16 rows take the ragged form");
   const uint32_t b = blockIdx.x;
   const int64_t i = b / slices;                     // row
   const int64_t l = (int64_t)(b - (uint32_t)i * slices) * 256 + threadIdx.x;   // lane: columns 4 l .. 4 l + 3
-  if (l >= lanes_per_row) return;                   // whole quads leave together (lanes_per_row % 4 == 0)
   const int64_t j0 = 4 * l;
-  const bool valid = j0 < a.cols;                   // cols % 4 == 0: all four columns valid or all padding
   uint32_t v[4] = {0u, 0u, 0u, 0u};
-  if (valid) {
-    u32x4 xw = {0u, 0u, 0u, 0u}, uw = {0u, 0u, 0u, 0u};
-    if (XT == 1) {
-      const uint32_t w = __builtin_nontemporal_load((const uint32_t*)((const int8_t*)a.x + i * a.x_rs + j0));
+  if constexpr (!RAGGED) {
+    if (l >= lanes_per_row) return;                 // whole quads leave together (lanes_per_row % 4 == 0)
+    const bool valid = j0 < a.cols;                 // cols % 4 == 0: all four columns valid or all padding
+    if (valid) {
+      u32x4 xw = {0u, 0u, 0u, 0u}, uw = {0u, 0u, 0u, 0u};
+      if (XT == 1) {
+        const uint32_t w = __builtin_nontemporal_load((const uint32_t*)((const int8_t*)a.x + i * a.x_rs + j0));
 #pragma unroll
-      for (int b = 0; b < 4; ++b) xw[b] = (uint32_t)(int32_t)(int8_t)(w >> (8 * b));
-    } else if (XT == 2) {
-      xw = __builtin_nontemporal_load((const u32x4*)((const uint32_t*)a.x + i * a.x_rs + j0));
+        for (int b = 0; b < 4; ++b) xw[b] = (uint32_t)(int32_t)(int8_t)(w >> (8 * b));
+      } else if (XT == 2) {
+        xw = __builtin_nontemporal_load((const u32x4*)((const uint32_t*)a.x + i * a.x_rs + j0));
+      }
+      if (F & MQ_U) uw = __builtin_nontemporal_load((const u32x4*)(a.u + i * a.ldu + j0));
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] = xw[b] + uw[b];
+      if (F & MQ_NOISE) {
+        uint32_t e[4];
+        sample4_aligned(a.noise, (uint64_t)i * (uint64_t)a.cols + (uint64_t)j0, e);
+        v[0] += e[0]; v[1] += e[1]; v[2] += e[2]; v[3] += e[3];
+      }
+      if (F & MQ_OUT) {
+        const u32x4 ov = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(ov, (u32x4*)(a.out + i * a.ldo + j0));
+      }
     }
-    if (F & MQ_U) uw = __builtin_nontemporal_load((const u32x4*)(a.u + i * a.ldu + j0));
+  } else {
+    const int64_t left = a.cols - j0;               // valid columns of this lane: min(left, 4), none if <= 0
+    if (left >= 4) {
+      u32x4 xw = {0u, 0u, 0u, 0u}, uw = {0u, 0u, 0u, 0u};
+      if (XT == 1) {
+        const uint32_t w = __builtin_nontemporal_load((const u32_any*)((const int8_t*)a.x + i * a.x_rs + j0));
 #pragma unroll
-    for (int b = 0; b < 4; ++b) v[b] = xw[b] + uw[b];
+        for (int b = 0; b < 4; ++b) xw[b] = (uint32_t)(int32_t)(int8_t)(w >> (8 * b));
+      } else if (XT == 2) {
+        xw = __builtin_nontemporal_load((const u32x4_any*)((const uint32_t*)a.x + i * a.x_rs + j0));
+      } else if (XT == 3) {
+        const auto w = __builtin_nontemporal_load((const u32x2_any*)((const int16_t*)a.x + i * a.x_rs + j0));
+        xw = u32x4{(uint32_t)(int32_t)(int16_t)w[0], (uint32_t)((int32_t)w[0] >> 16),
+                   (uint32_t)(int32_t)(int16_t)w[1], (uint32_t)((int32_t)w[1] >> 16)};
+      }
+      if (F & MQ_U) uw = __builtin_nontemporal_load((const u32x4_any*)(a.u + i * a.ldu + j0));
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] = xw[b] + uw[b];
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (b >= left) continue;
+        if (XT == 1) v[b] = (uint32_t)(int32_t)((const int8_t*)a.x)[i * a.x_rs + j0 + b];
+        else if (XT == 2) v[b] = ((const uint32_t*)a.x)[i * a.x_rs + j0 + b];
+        else if (XT == 3) v[b] = (uint32_t)(int32_t)((const int16_t*)a.x)[i * a.x_rs + j0 + b];
+        if (F & MQ_U) v[b] += a.u[i * a.ldu + j0 + b];
+      }
+    }
     if (F & MQ_NOISE) {
+      const RngArgs& r = a.noise;
+      const uint64_t row0 = (uint64_t)i * (uint64_t)a.cols;     // element of the row's first column
       uint32_t e[4];
-      sample4_aligned(a.noise, (uint64_t)i * (uint64_t)a.cols + (uint64_t)j0, e);
-      v[0] += e[0]; v[1] += e[1]; v[2] += e[2]; v[3] += e[3];
+      if (r.dist == 3) {
+        sparse4_any(r, row0 + (uint64_t)j0, e);
+      } else {
+        const int s = (int)(row0 & 3);
+        const uint64_t blk = (row0 >> 2) + (uint64_t)l;
+        const uint4 p = philox_block(r, blk);
+        e[0] = p.x; e[1] = p.y; e[2] = p.z; e[3] = p.w;
+        if (s != 0) {                                 // uniform: one row per workgroup
+          __shared__ uint4 blocks[257];
+          blocks[threadIdx.x] = p;
+          if (threadIdx.x == 255) blocks[256] = philox_block(r, blk + 1);
+          __syncthreads();
+          const uint4 q = blocks[threadIdx.x + 1];
+          const uint32_t w[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+#pragma unroll
+          for (int b = 0; b < 4; ++b) e[b] = s == 1 ? w[b + 1] : s == 2 ? w[b + 2] : w[b + 3];
+        }
+        if (r.dist == 2) dgauss4(r, e);
+      }
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] += e[b];
     }
-    if (F & MQ_OUT) {
-      const u32x4 ov = {v[0], v[1], v[2], v[3]};
-      __builtin_nontemporal_store(ov, (u32x4*)(a.out + i * a.ldo + j0));
+    if (l >= lanes_per_row) return;                 // whole quads leave together
+    if (left >= 4) {
+      if (F & MQ_OUT) {
+        const u32x4 ov = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(ov, (u32x4_any*)(a.out + i * a.ldo + j0));
+      }
+    } else {
+#pragma unroll
+      for (int b = 0; b < 4; ++b) {
+        if (b >= left) v[b] = 0u;                   // padding columns of a digit group are zero
+        else if (F & MQ_OUT) a.out[i * a.ldo + j0 + b] = v[b];
+      }
     }
   }
   if (F & MQ_DIG) {
@@ -184,22 +265,23 @@ __global__ __launch_bounds__(256) void mask_quad_kernel(MaskLaunch a, int64_t la
   }
 }
 
-template <int XT, int F>
+template <int XT, int F, bool RAGGED>
 void launch_mask_quad(uint32_t slices, const MaskLaunch& a, int64_t lanes_per_row, hipStream_t s) {
-  hipLaunchKernelGGL((mask_quad_kernel<XT, F>), dim3((unsigned)(a.rows * slices)), dim3(256), 0, s, a,
+  hipLaunchKernelGGL((mask_quad_kernel<XT, F, RAGGED>), dim3((unsigned)(a.rows * slices)), dim3(256), 0, s, a,
                      lanes_per_row, slices);
 }
 
 typedef void (*MaskQuadLaunch)(uint32_t, const MaskLaunch&, int64_t, hipStream_t);
 
-template <int XT>
+// At least one output is present: F is 4 to 15.
+template <int XT, bool RG>
 MaskQuadLaunch mask_quad_for(int f) {
-  static const MaskQuadLaunch table[16] = {
-      launch_mask_quad<XT, 0>,  launch_mask_quad<XT, 1>,  launch_mask_quad<XT, 2>,  launch_mask_quad<XT, 3>,
-      launch_mask_quad<XT, 4>,  launch_mask_quad<XT, 5>,  launch_mask_quad<XT, 6>,  launch_mask_quad<XT, 7>,
-      launch_mask_quad<XT, 8>,  launch_mask_quad<XT, 9>,  launch_mask_quad<XT, 10>, launch_mask_quad<XT, 11>,
-      launch_mask_quad<XT, 12>, launch_mask_quad<XT, 13>, launch_mask_quad<XT, 14>, launch_mask_quad<XT, 15>};
-  return table[f & 15];
+  static const MaskQuadLaunch table[12] = {
+      launch_mask_quad<XT, 4, RG>,  launch_mask_quad<XT, 5, RG>,  launch_mask_quad<XT, 6, RG>,
+      launch_mask_quad<XT, 7, RG>,  launch_mask_quad<XT, 8, RG>,  launch_mask_quad<XT, 9, RG>,
+      launch_mask_quad<XT, 10, RG>, launch_mask_quad<XT, 11, RG>, launch_mask_quad<XT, 12, RG>,
+      launch_mask_quad<XT, 13, RG>, launch_mask_quad<XT, 14, RG>, launch_mask_quad<XT, 15, RG>};
+  return table[(f & 15) - 4];
 }
 
 __global__ __launch_bounds__(256) void signs_kernel(RngArgs r, int64_t n, int8_t* out) {
@@ -267,23 +349,32 @@ __global__ __launch_bounds__(256) void unmask_elementwise_kernel(GemmLaunch g) {
 }  // namespace
 
 hipError_t launch_mask(const MaskLaunch& a, hipStream_t s) {
-  // fast path: see mask_quad_kernel
+  // contiguous rows take mask_quad_kernel, its ragged form unless every row of
+  // every operand starts on a lane's own alignment (16 bytes of words, 4 of
+  // int8) and ends with a whole lane: the aligned form is the faster one there
+  // (no LDS, no partial lanes) and the ragged one cannot be needed
+  const bool x_row = a.x == nullptr || a.x_cs == 1;
   const bool x_ok = a.x == nullptr ||
-                    (a.x_cs == 1 && a.x_dtype == 0 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 3) == 0) ||
-                    (a.x_cs == 1 && a.x_dtype >= 2 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 15) == 0);
+                    (a.x_dtype == 0 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 3) == 0) ||
+                    (a.x_dtype >= 2 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 15) == 0);
   const bool u_ok = a.u == nullptr || (a.ldu % 4 == 0 && ((uintptr_t)a.u & 15) == 0);
   const bool o_ok = a.out == nullptr || (a.ldo % 4 == 0 && ((uintptr_t)a.out & 15) == 0);
   const bool n_ok = !a.has_noise || !a.noise.transposed;
   const int64_t lanes_per_row = (a.dig != nullptr) ? 64 * ((a.cols + 63) / 64) / 4 : 4 * ((a.cols + 15) / 16);
   const int64_t blocks_per_row = (lanes_per_row + 255) / 256;
-  if (a.cols % 4 == 0 && x_ok && u_ok && o_ok && n_ok && a.rows * blocks_per_row <= 0x7FFFFFFF) {
+  if (x_row && n_ok && a.rows * blocks_per_row <= 0x7FFFFFFF) {
     if (a.rows == 0 || lanes_per_row == 0) return hipSuccess;
     const uint32_t slices = (uint32_t)blocks_per_row;
     const int f = (a.u != nullptr ? MQ_U : 0) | (a.has_noise ? MQ_NOISE : 0) | (a.out != nullptr ? MQ_OUT : 0) |
                   (a.dig != nullptr ? MQ_DIG : 0);
-    if (a.x == nullptr) mask_quad_for<0>(f)(slices, a, lanes_per_row, s);
-    else if (a.x_dtype == 0) mask_quad_for<1>(f)(slices, a, lanes_per_row, s);
-    else mask_quad_for<2>(f)(slices, a, lanes_per_row, s);
+    const int xt = a.x == nullptr ? 0 : a.x_dtype == 0 ? 1 : a.x_dtype == 1 ? 3 : 2;
+    MaskQuadLaunch go;
+    if (a.cols % 4 == 0 && x_ok && u_ok && o_ok)
+      go = xt == 0 ? mask_quad_for<0, false>(f) : xt == 1 ? mask_quad_for<1, false>(f) : mask_quad_for<2, false>(f);
+    else
+      go = xt == 0 ? mask_quad_for<0, true>(f) : xt == 1 ? mask_quad_for<1, true>(f)
+         : xt == 2 ? mask_quad_for<2, true>(f) : mask_quad_for<3, true>(f);
+    go(slices, a, lanes_per_row, s);
     return hipGetLastError();
   }
   const int64_t groups = (a.dig != nullptr) ? (64 * ((a.cols + 63) / 64)) / 16 : (a.cols + 15) / 16;
