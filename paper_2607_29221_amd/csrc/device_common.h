@@ -176,6 +176,22 @@ __device__ __forceinline__ void sparse4_any(const RngArgs& r, uint64_t e0, uint3
   }
 }
 
+// Elements e0 .. e0+3, e0 any: two blocks where e0 is not a multiple of 4.
+__device__ __forceinline__ void sample4_any(const RngArgs& r, uint64_t e0, uint32_t out[4]) {
+  if ((e0 & 3) == 0) {
+    sample4_aligned(r, e0, out);
+  } else if (r.dist == 3) {
+    sparse4_any(r, e0, out);
+  } else {
+    const uint4 p = philox_block(r, e0 >> 2), q = philox_block(r, (e0 >> 2) + 1);
+    const uint32_t w[8] = {p.x, p.y, p.z, p.w, q.x, q.y, q.z, q.w};
+    const int s = (int)(e0 & 3);
+#pragma unroll
+    for (int b = 0; b < 4; ++b) out[b] = s == 1 ? w[b + 1] : s == 2 ? w[b + 2] : w[b + 3];
+    if (r.dist == 2) dgauss4(r, out);
+  }
+}
+
 // Balanced base-256 digits of x packed in one word: byte t is digit t as an
 // int8. Adding 0x80 to every byte position maps each balanced digit d to the
 // ordinary byte d + 128 of x + 0x80808080; flipping bit 7 of every byte

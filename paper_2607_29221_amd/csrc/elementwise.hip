@@ -2,11 +2,9 @@
 // elements and/or digit layout), sampling (the same pass with only e), the
 // rotation's sign vector, and unmasking without a product term.
 //
-// One thread owns one 16-column digit group of one row: it reads 16 plaintext
-// values, 16 ring words of u, draws 16 noise values (four Philox blocks when
-// the group starts on a block boundary), and writes the four 16-byte digit
-// planes of the group -- contiguous 64-byte chunks, so a wave writes 4 KiB of
-// consecutive memory.
+// Contiguous rows take mask_quad_kernel, transposed plaintext and samples
+// mask_turn_kernel, anything else (plaintext with two strides, one of
+// plaintext and noise transposed) the general mask_kernel.
 #include "internal.h"
 
 namespace mosaic {
@@ -21,6 +19,10 @@ __device__ __forceinline__ uint32_t load_x(const void* x, int32_t dt, int64_t of
   }
 }
 
+// General form. One thread owns one 16-column digit group of one row: it reads
+// 16 plaintext values, 16 ring words of u, draws 16 noise values (four Philox
+// blocks when the group starts on a block boundary), and writes the four
+// 16-byte digit planes of the group.
 __global__ __launch_bounds__(256) void mask_kernel(MaskLaunch a, int64_t groups) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = gid / groups;
@@ -148,10 +150,10 @@ __global__ __launch_bounds__(256) void mask_kernel(MaskLaunch a, int64_t groups)
 // s = (row cols) % 4 of a Philox block, the same s for the whole workgroup
 // (one row each): every lane draws one block and takes its neighbour's through
 // LDS, and only the last wave draws one more, so the draws grow by a quarter
-// where two blocks a lane would double them. The general kernel below, one
+// where two blocks a lane would double them. The general kernel above, one
 // thread per 16 columns with 4-byte accesses 64 bytes apart and one Philox
-// block per element, took 39 us for 1000 x 5003 codes with u and noise (60 MB,
-// 1.5 TB/s).
+// block per element, took 39 us for 1000 x 5003 codes with u and noise (60 MB)
+// against 15 us here.
 enum { MQ_U = 1, MQ_NOISE = 2, MQ_OUT = 4, MQ_DIG = 8 };
 // Workgroup b covers 1024-column slice b % slices of row b / slices, so
 // consecutive workgroups stream consecutive memory (79% of the HBM peak
@@ -190,7 +192,7 @@ __global__ __launch_bounds__(256) void mask_quad_kernel(MaskLaunch a, int64_t la
       }
     }
   } else {
-    const int64_t left = a.cols - j0;               // valid columns of this lane: min(left, 4), none if <= 0
+    const int64_t left = a.cols - j0;               // columns present: min(left, 4), none if <= 0
     if (left >= 4) {
       u32x4 xw = {0u, 0u, 0u, 0u}, uw = {0u, 0u, 0u, 0u};
       if (XT == 1) {
@@ -284,6 +286,118 @@ MaskQuadLaunch mask_quad_for(int f) {
   return table[(f & 15) - 4];
 }
 
+// Mask pass whose plaintext lies transposed in memory (consecutive rows i of
+// the result are consecutive elements, x_rs = 1) and whose noise, if any, is
+// that of the transposed matrix: element (i, j) of the result is x[i + j x_cs]
+// plus element e = j rows + i of the stream. A workgroup owns a 64 x 64 tile
+// of the result: it reads (or draws) four consecutive i of one j per lane,
+// 256 contiguous bytes of words per j, turns the tile through LDS, and then
+// adds u and writes words and digits as the kernel above does, four columns
+// per lane, 256 contiguous bytes per row. The pitch of 65 words makes both
+// sides of the exchange free of bank conflicts: the writes of a wave fall in
+// banks 4 a + j + b, its reads in banks i + 4 q + b. Bound by HBM; the general
+// kernel, whose lanes read x at a row pitch from each other and drew a Philox
+// block per element, took 126 us for 4096 x 4096 words to digits (128 MiB,
+// 1.1 TB/s) against 28 us here, and 22 us for a transposed 4096 x 1536
+// uniform sample against 10.
+template <int XT, bool NOISE>
+__global__ __launch_bounds__(256) void mask_turn_kernel(MaskLaunch a, uint32_t tiles_j) {
+  constexpr int LD = 65;
+  __shared__ uint32_t t[64 * LD];
+  const int64_t ti = blockIdx.x / tiles_j;
+  const int64_t i0 = 64 * ti, j0 = 64 * (int64_t)(blockIdx.x - (uint32_t)ti * tiles_j);
+  const int lane4 = 4 * (threadIdx.x & 15);            // first of this lane's four elements of a tile line
+  const int line = threadIdx.x >> 4;                   // tile line within a pass of 16
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int jj = 16 * p + line;
+    const int64_t j = j0 + jj, i = i0 + lane4;
+    const int64_t left = j < a.cols ? a.rows - i : 0;  // elements present: min(left, 4)
+    uint32_t v[4] = {0u, 0u, 0u, 0u};
+    if (XT != 0) {
+      const int64_t off = i + j * a.x_cs;
+      if (left >= 4) {
+        if (XT == 1) {
+          const uint32_t w = __builtin_nontemporal_load((const u32_any*)((const int8_t*)a.x + off));
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = (uint32_t)(int32_t)(int8_t)(w >> (8 * b));
+        } else if (XT == 2) {
+          const u32x4 w = __builtin_nontemporal_load((const u32x4_any*)((const uint32_t*)a.x + off));
+#pragma unroll
+          for (int b = 0; b < 4; ++b) v[b] = w[b];
+        } else {
+          const auto w = __builtin_nontemporal_load((const u32x2_any*)((const int16_t*)a.x + off));
+          v[0] = (uint32_t)(int32_t)(int16_t)w[0]; v[1] = (uint32_t)((int32_t)w[0] >> 16);
+          v[2] = (uint32_t)(int32_t)(int16_t)w[1]; v[3] = (uint32_t)((int32_t)w[1] >> 16);
+        }
+      } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+          if (b >= left) continue;
+          if (XT == 1) v[b] = (uint32_t)(int32_t)((const int8_t*)a.x)[off + b];
+          else if (XT == 2) v[b] = ((const uint32_t*)a.x)[off + b];
+          else v[b] = (uint32_t)(int32_t)((const int16_t*)a.x)[off + b];
+        }
+      }
+    }
+    if (NOISE && left > 0) {
+      uint32_t e[4];
+      sample4_any(a.noise, (uint64_t)j * (uint64_t)a.rows + (uint64_t)i, e);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) v[b] += e[b];
+    }
+#pragma unroll
+    for (int b = 0; b < 4; ++b) t[(lane4 + b) * LD + jj] = v[b];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int p = 0; p < 4; ++p) {
+    const int ii = 16 * p + line;
+    const int64_t i = i0 + ii, j = j0 + lane4;
+    if (i >= a.rows) break;                            // the 16 lanes of a row leave together
+    const int64_t left = a.cols - j;
+    uint32_t v[4];
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v[b] = b < left ? t[ii * LD + lane4 + b] : 0u;
+    if (a.u != nullptr) {
+      const uint32_t* up = a.u + i * a.ldu + j;
+      if (left >= 4) {
+        const u32x4 w = __builtin_nontemporal_load((const u32x4_any*)up);
+#pragma unroll
+        for (int b = 0; b < 4; ++b) v[b] += w[b];
+      } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (b < left) v[b] += up[b];
+      }
+    }
+    if (a.out != nullptr) {
+      uint32_t* op = a.out + i * a.ldo + j;
+      if (left >= 4) {
+        const u32x4 ov = {v[0], v[1], v[2], v[3]};
+        __builtin_nontemporal_store(ov, (u32x4_any*)op);
+      } else {
+#pragma unroll
+        for (int b = 0; b < 4; ++b)
+          if (b < left) op[b] = v[b];
+      }
+    }
+    if (a.dig != nullptr) {                            // the row's padding columns lie in its last tile
+      uint32_t o[4];
+      quad_digit_planes(v, threadIdx.x & 3, o);
+      const u32x4 ov = {o[0], o[1], o[2], o[3]};
+      __builtin_nontemporal_store(ov, (u32x4*)(a.dig + i * a.pitch + 4 * j));
+    }
+  }
+}
+
+template <int XT>
+void launch_mask_turn(const MaskLaunch& a, uint32_t tiles_i, uint32_t tiles_j, hipStream_t s) {
+  const dim3 grid(tiles_i * tiles_j);
+  if (a.has_noise) hipLaunchKernelGGL((mask_turn_kernel<XT, true>), grid, dim3(256), 0, s, a, tiles_j);
+  else hipLaunchKernelGGL((mask_turn_kernel<XT, false>), grid, dim3(256), 0, s, a, tiles_j);
+}
+
 __global__ __launch_bounds__(256) void signs_kernel(RngArgs r, int64_t n, int8_t* out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t e0 = 4 * i;
@@ -375,6 +489,18 @@ hipError_t launch_mask(const MaskLaunch& a, hipStream_t s) {
       go = xt == 0 ? mask_quad_for<0, true>(f) : xt == 1 ? mask_quad_for<1, true>(f)
          : xt == 2 ? mask_quad_for<2, true>(f) : mask_quad_for<3, true>(f);
     go(slices, a, lanes_per_row, s);
+    return hipGetLastError();
+  }
+  // transposed plaintext and transposed noise (or one of them alone): tiles
+  // turned through LDS; what remains for the general kernel is one of them
+  // transposed and the other not, and plaintext with two strides
+  const int64_t tiles_i = (a.rows + 63) / 64, tiles_j = (a.cols + 63) / 64;
+  if ((a.x == nullptr || a.x_rs == 1) && (!a.has_noise || a.noise.transposed) && tiles_i <= 0x7FFFFFFF / tiles_j) {
+    const uint32_t ti = (uint32_t)tiles_i, tj = (uint32_t)tiles_j;
+    if (a.x == nullptr) launch_mask_turn<0>(a, ti, tj, s);
+    else if (a.x_dtype == 0) launch_mask_turn<1>(a, ti, tj, s);
+    else if (a.x_dtype == 1) launch_mask_turn<3>(a, ti, tj, s);
+    else launch_mask_turn<2>(a, ti, tj, s);
     return hipGetLastError();
   }
   const int64_t groups = (a.dig != nullptr) ? (64 * ((a.cols + 63) / 64)) / 16 : (a.cols + 15) / 16;

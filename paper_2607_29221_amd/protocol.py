@@ -119,11 +119,16 @@ class MaskedWeight:
         slot_of = {lv: k for k, lv in enumerate(self.slot_levels)}
         # destinations: the server's Bext rows, and the client's concatenated
         # factors (one buffer each, slots side by side)
-        self.Bext = Digits(torch.zeros((N + self.R, 4 * Kp), dtype=torch.int8, device=dev), K)
+        self.Bext = Digits(torch.empty((N + self.R, 4 * Kp), dtype=torch.int8, device=dev), K)
+        # (N_1 ... N_i)^T (r_i x K), the slots below each other as in Bext
+        NcT = Digits(torch.empty((self.R, 4 * Kp), dtype=torch.int8, device=dev), K)
         self.q_cols, row = [], N
         for ri in self.slot_ranks:
             self.q_cols.append(row)          # column of this slot's Q in [Y' | Q]
             row += padded_k(ri)
+            if row > self.q_cols[-1] + ri:   # padding rows are zero
+                self.Bext.buf[self.q_cols[-1] + ri: row].zero_()
+                NcT.buf[self.q_cols[-1] + ri - N: row - N].zero_()
         self.n_out = N + self.R
         McTcat = Digits.concat(K, self.slot_ranks, dev)
         bx = torch.empty((K + N, 4 * max(self.R, 64)), dtype=torch.int8, device=dev)
@@ -151,10 +156,12 @@ class MaskedWeight:
                 if not self.keep_dense:                       # U_w then needs S_{i+1} Mc_i by gathering
                     Mc32[i] = _ring_empty(r[i - 1], K, dev)
 
-        NcT: List[Digits] = []                # (N_1 ... N_i)^T (r_i x K)
+        def nct_dst(i):   # (N_1 ... N_i)^T (r_i x K): rows of NcT
+            r0 = slot_col[slot_of[i]]
+            return Digits(NcT.buf[r0: r0 + r[i - 1]], K)
+
         for i in range(1, d + 1):
             ri = r[i - 1]
-            nct = Digits.empty(ri, K, dev)
             keep = i in Mc32
             keep_d = i in self.D
             if i == 1:
@@ -162,21 +169,23 @@ class MaskedWeight:
                                 out=Mc32[1] if keep else None)
                 m.mosaic_sample(m.rng(s, STREAM_M + 1, weight_id, U, transposed=True), K, ri, out_dig=mct_dst(1))
                 m.mosaic_sample(m.rng(s, STREAM_N + 1, weight_id, U), K, ri, out_dig=nc_dst(1))
-                m.mosaic_sample(m.rng(s, STREAM_N + 1, weight_id, U, transposed=True), ri, K, out_dig=nct,
+                m.mosaic_sample(m.rng(s, STREAM_N + 1, weight_id, U, transposed=True), ri, K, out_dig=nct_dst(1),
                                 out=self.D[1][:, :K] if keep_d else None)
             else:
+                # each chain is multiplied once, M_i Mc_{i-1} and N_i^T Nc_{i-1}^T,
+                # and written in digits both as it is and transposed
                 rp = r[i - 2]
                 Mi = Digits.empty(ri, rp, dev)                  # M_i (r_i x r_{i-1})
                 NiT = Digits.empty(ri, rp, dev)                 # N_i^T
                 m.mosaic_sample(m.rng(s, STREAM_M + i, weight_id, U), ri, rp, out_dig=Mi)
                 m.mosaic_sample(m.rng(s, STREAM_N + i, weight_id, U, transposed=True), ri, rp, out_dig=NiT)
-                self._product_to_digits(Mi, mct_dst(i - 1), ri, K, rp, mc_dst(i),
-                                        Mc32[i] if keep else None)                      # M_i Mc_{i-1}
-                self._product_to_digits(mct_dst(i - 1), Mi, K, ri, rp, mct_dst(i))   # McT_{i-1} M_i^T
-                self._product_to_digits(nc_dst(i - 1), NiT, K, ri, rp, nc_dst(i))    # Nc_{i-1} N_i
-                self._product_to_digits(NiT, nc_dst(i - 1), ri, K, rp, nct,
-                                        self.D[i][:, :K] if keep_d else None)          # N_i^T Nc_{i-1}^T
-            NcT.append(nct)
+                for f, prev, same, turned, words in (
+                        (Mi, mct_dst(i - 1), mc_dst(i), mct_dst(i), Mc32[i] if keep else None),
+                        (NiT, nc_dst(i - 1), nct_dst(i), nc_dst(i), self.D[i][:, :K] if keep_d else None)):
+                    words = _ring_empty(ri, K, dev) if words is None else words
+                    m.mosaic_masked_matmul(f, prev, ri, K, rp, words)
+                    m.mosaic_mask(None, words, None, ri, K, out_dig=same)
+                    m.mosaic_mask(words, None, None, K, ri, out_dig=turned, x_transposed=True)
 
         # client: Lcat = [L | S_2 | ... | S_d] (sparse-only: L alone), and
         # S_{i+1} as compressed rows when the sparse form is kept
@@ -236,17 +245,18 @@ class MaskedWeight:
             m.mosaic_mask(key_w, key_q, None, self.t, K, out_dig=self.cT)
             del key_w, key_q
 
-        # client: J_i = (W + E_w) Nc_i, stored in the lower rows of Bx
+        # client: J_i = (W + E_w) Nc_i, every level in one product (the padding
+        # rows of NcT give zero columns), stored in the lower rows of Bx
         WE = Digits.empty(N, K, dev)
         m.mosaic_mask(W, None, ew, N, K, out_dig=WE)
-        for lv in range(1, d + 1):
-            ri = r[lv - 1]
-            J = _ring_empty(N, ri, dev)
-            m.mosaic_masked_matmul(WE, NcT[lv - 1], N, ri, K, J)
-            m.mosaic_mask(None, J, None, N, ri, out_dig=Digits(bx[K:], ri, slot_col[slot_of[lv]]))
-            if lv in self.D:                                  # J_i^T next to (N_1..N_i)^T
-                m.mosaic_masked_matmul(NcT[lv - 1], WE, ri, N, K, self.D[lv][:, K:])
+        J = _ring_empty(N, self.R, dev)
+        m.mosaic_masked_matmul(WE, NcT, N, self.R, K, J)
         del WE, NcT
+        m.mosaic_mask(None, J, None, N, self.R, out_dig=Digits(bx[K:], self.R))
+        for lv, D in self.D.items():                          # J_i^T next to (N_1..N_i)^T
+            c0 = slot_col[slot_of[lv]]
+            m.mosaic_mask(J[:, c0: c0 + r[lv - 1]], None, None, r[lv - 1], N, out=D[:, K:], x_transposed=True)
+        del J
         self.Bx_dense = Digits(bx, r[d - 1])     # the level-d slot (sparse calls)
 
     def sparse_call(self, M: int) -> bool:
@@ -256,14 +266,6 @@ class MaskedWeight:
         if not self.keep_dense:
             return True
         return M <= SPARSE_LPN_MAX_TOKENS
-
-    @staticmethod
-    def _product_to_digits(a: Digits, b: Digits, rows: int, cols: int, inner: int, out: Digits,
-                           words: Optional[torch.Tensor] = None) -> None:
-        """out = digits of a b^T; ``words`` (optional) receives the ring words."""
-        tmp = _ring_empty(rows, cols, a.buf.device) if words is None else words
-        m.mosaic_masked_matmul(a, b, rows, cols, inner, tmp)
-        m.mosaic_mask(None, tmp, None, rows, cols, out_dig=out)
 
 
 @dataclass

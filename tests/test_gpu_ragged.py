@@ -68,3 +68,39 @@ def test_quantize_ragged(n, offset):
     assert np.array_equal(got[:, offset: offset + n], qr)
     assert np.all(got[:, :offset] == 77) and np.all(got[:, offset + n:] == 77)
     assert np.array_equal(unpack_digits(dig), qr.view(np.uint32)) and pad_is_zero(dig)
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 9), (3, 65), (64, 64), (63, 130), (66, 1), (130, 67), (257, 300)])
+@pytest.mark.parametrize("kind", [None, "uniform", "dgauss", "sparse"])
+@pytest.mark.parametrize("dtype", ["none", "int8", "int16", "int32"])
+def test_mask_transposed(rows, cols, kind, dtype):
+    """Plaintext stored transposed and noise of the transposed matrix, at tile
+    edges (64 x 64), row counts that are not multiples of 4 and offsets."""
+    from oracle import sampling as smp
+    if dtype == "none" and kind is None:
+        pytest.skip("neither plaintext nor noise")
+    rng = np.random.default_rng(rows * 31 + cols)
+    want = np.zeros((rows, cols), np.int64)
+    x = None
+    if dtype != "none":
+        info = np.iinfo(dtype)
+        x = rng.integers(info.min, info.max + 1, (cols, rows + 3)).astype(dtype)
+        want = want + x[:, 1: 1 + rows].T.astype(np.int64)
+    u = rng.integers(0, 2 ** 32, (rows, cols + 1), dtype=np.uint32) if cols % 2 else None
+    if u is not None:
+        want = want + u[:, 1:].astype(np.int64)
+    noise = None
+    if kind is not None:
+        noise = m.rng(17, 0x31, 2, KINDS[kind], sigma=0.5, bound=4, log2_inv_density=2, transposed=True)
+        want = want + smp.sample_matrix(kind, cols, rows, 17, 0x31, 2, sigma=0.5, bound=4,
+                                        log2_inv_density=2).T.astype(np.int64)
+    want = (want & 0xFFFFFFFF).astype(np.uint32)
+    out = torch.full((rows, cols + 2), 77, dtype=torch.int32, device="cuda")
+    dig = Digits.empty(rows, cols)
+    m.mosaic_mask(None if x is None else torch.from_numpy(x).cuda()[:, 1: 1 + rows],
+                  None if u is None else to_dev_ring(u)[:, 1:], noise, rows, cols,
+                  out=out[:, 1: 1 + cols], out_dig=dig, x_transposed=x is not None)
+    got = to_np_u32(out)
+    assert np.array_equal(got[:, 1: 1 + cols], want)
+    assert np.all(got[:, 0] == 77) and np.all(got[:, 1 + cols:] == 77)
+    assert np.array_equal(unpack_digits(dig), want) and pad_is_zero(dig)
