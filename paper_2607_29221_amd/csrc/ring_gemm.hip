@@ -15,34 +15,39 @@
 // longer inner dimensions into chunks whose products are added into C
 // (EPI_ACCUM).
 //
-// Work decomposition. A block of 512 threads (8 waves, two per SIMD) owns a
-// 128 x 128 output tile; wave w computes rows 64 (w / 4) .. +64 and columns
-// 32 (w % 4) .. +32 as two 32 x 32 tiles of v_mfma_i32_32x32x32_i8, holding
-// 2 tiles x 4 shift classes x 16 = 128 accumulator registers. Two waves per
-// SIMD let one wave's MFMAs run while the other waits at a barrier or on LDS.
+// Work decomposition. A wave computes 64 rows x 32 columns as two 32 x 32
+// tiles of v_mfma_i32_32x32x32_i8, holding 2 tiles x 4 shift classes x 16 =
+// 128 accumulator registers; four waves side by side make a row of waves, 64
+// x 128 outputs. The kernel comes in three forms (struct Form), chosen by
+// choose_plan. FORM_128: two rows of waves, a 128 x 128 output tile, four
+// stages in LDS; two waves per SIMD let one wave's MFMAs run while the other
+// waits at a barrier or on LDS. FORM_64K: one row of waves twice, a 64 x 128
+// tile whose stages the two groups of waves take in turn, three stages of
+// each group in LDS; the groups' products meet in LDS at the end. FORM_64:
+// one row of waves, three stages in LDS, so that two workgroups share a
+// compute unit.
 //
 // Pipeline. The K dimension is consumed in stages of 32 columns (128 bytes
-// per row per operand). Four stages live in LDS at once (4 x 32 KiB) and are
-// filled by direct buffer-to-LDS loads issued four stages ahead: stage s's
-// fragments are read into registers during stage s-1, so once the barrier
-// before stage s has passed, its slot is free and the loads of stage s+4 go
-// there. Each wave runs a stage as four groups of 5 MFMAs, pinned by
-// scheduling barriers: the 12 LDS reads of stage s+1's fragments follow the
-// first three groups (four each), so they have completed by the time the
-// next barrier needs them, and one of the wave's 4 direct loads follows
-// each group (whole bench steps over the three server shapes 1.2-1.6%
+// per row per operand). NST stages of a group live in LDS at once (FORM_128:
+// 4 x 32 KiB) and are filled by direct buffer-to-LDS loads issued NST stages
+// ahead: stage s's fragments are read into registers during stage s-1, so
+// once the barrier before stage s has passed, its slot is free and the loads
+// of stage s+NST go there. Each wave runs a stage as four groups of 5 MFMAs,
+// pinned by scheduling barriers: the 12 LDS reads of stage s+1's fragments
+// follow the first three groups (four each), so they have completed by the
+// time the next barrier needs them, and one of the wave's 4 direct loads
+// follows each group (whole bench steps over the three server shapes 1.2-1.6%
 // faster than with the 4 loads after the first two groups, 0.3-0.5% faster
 // than with one load and three reads after every group, 4% faster than with
 // six reads after each of the first two). The fragments are double-buffered in
 // registers. One barrier per stage publishes stage s+1 and retires the slot
 // of stage s, which the loads of stage s then refill. All stages but the
-// last four run in a loop with no tests (every stage refills and reads),
-// four stages per iteration. LDS holds the A tiles of the four slots first
-// and then their B tiles (16 KiB each), so that every fragment read
-// addresses its slot and tile by an immediate offset from one of the
-// lane's eight fragment offsets: that loop computes no addresses in vector
-// registers (0.8% faster whole bench steps than slots of A and B together,
-// whose third and fourth slots lie beyond the 64 KiB offset range).
+// last ones run in a loop with no tests (every stage refills and reads). LDS
+// holds the A tiles of a group's slots first and then their B tiles, so that
+// every fragment read addresses its slot and tile by an immediate offset from
+// one of the lane's eight fragment offsets: that loop computes no addresses in
+// vector registers (0.8% faster whole bench steps than slots of A and B
+// together, whose third and fourth slots lie beyond the 64 KiB offset range).
 //
 // LDS rows are 128 bytes (8 chunks of 16 bytes); chunk c of row R sits in
 // slot c ^ ((R >> 1) & 7). Sixteen lanes reading one chunk of 16 consecutive
@@ -63,15 +68,28 @@ namespace {
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef int v16i __attribute__((ext_vector_type(16)));
 
-constexpr int BM = 128;              // block tile rows (A)
 constexpr int BN = 128;              // block tile rows (B) = output columns
-constexpr int NTHREADS = 512;
 constexpr int BK = 32;               // columns per stage
 constexpr int ROWB = BK * 4;         // bytes per row per stage
-constexpr int OPS = BM * ROWB;       // one operand stage in LDS (16 KiB)
-constexpr int STAGE = 2 * OPS;       // A and B (32 KiB)
-constexpr int NSTAGE = 4;            // stages resident in LDS
 constexpr uint32_t kRsrcWord3 = 0x00020000u;
+
+// A form of the kernel: a tile of 64 WMR x 128 outputs, WMR rows of four
+// waves; KW such groups of waves, group kw taking stages kw, kw + KW, ...; NST
+// stages of each group resident in LDS.
+template <int WMR_, int KW_, int NST_>
+struct Form {
+  static constexpr int WMR = WMR_, KW = KW_, NST = NST_;
+  static constexpr int BM = 64 * WMR;            // block tile rows (A)
+  static constexpr int NW = 4 * WMR;             // waves of a group
+  static constexpr int NT = 64 * NW * KW;        // threads
+  static constexpr int OPA = BM * ROWB;          // A part of a stage in LDS
+  static constexpr int OPB = BN * ROWB;          // B part (16 KiB)
+  static constexpr int GRP = NST * (OPA + OPB);  // LDS of a group
+  static constexpr int RB = BN / NW;             // B rows that a wave loads (of A always 16)
+  static constexpr int NL = 2 + RB / 8;          // direct loads per wave per stage
+  static constexpr int UN = NST % 2 ? 2 * NST : NST;   // stages per iteration of the steady loop
+  static_assert(KW * GRP <= 160 * 1024 && BM * (BN + 4) * 4 <= KW * GRP, "LDS");
+};
 
 struct Tile {
   int64_t tm, tn;
@@ -126,38 +144,41 @@ __device__ __forceinline__ v4i make_rsrc(const void* base, int64_t bytes) {
   return v4i{(int)(uint32_t)b, (int)((uint32_t)(b >> 32) & 0xFFFFu), (int)bytes, (int)kRsrcWord3};
 }
 
-// s_waitcnt with only the vector-memory counter constrained: at most 4 n
-// direct loads of this wave (n stages) may still be in flight.
+// s_waitcnt with only the vector-memory counter constrained: vmcnt(N)
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
+// At most n stages of this wave's NL direct loads each may still be in flight.
+template <int NL>
 __device__ __forceinline__ void wait_loads(int n) {
-  if (n >= 3) __builtin_amdgcn_s_waitcnt(0x0F7C);        // vmcnt(12)
-  else if (n == 2) __builtin_amdgcn_s_waitcnt(0x0F78);   // vmcnt(8)
-  else if (n == 1) __builtin_amdgcn_s_waitcnt(0x0F74);   // vmcnt(4)
-  else __builtin_amdgcn_s_waitcnt(0x0F70);               // vmcnt(0)
+  if (n >= 5) wait_vm<5 * NL>();
+  else if (n == 4) wait_vm<4 * NL>();
+  else if (n == 3) wait_vm<3 * NL>();
+  else if (n == 2) wait_vm<2 * NL>();
+  else if (n == 1) wait_vm<NL>();
+  else wait_vm<0>();
 }
 
 __device__ __forceinline__ int imin(int a, int b) { return a < b ? a : b; }
 
 // Adds a TM x TN tile held in LDS (row pitch TROW words) into C with 32-bit
-// atomics (wrap-around adds: exact over the ring), chunks of 4 columns as in
-// gemm_tile_epilogue.
+// atomics (wrap-around adds: exact over the ring), consecutive lanes on
+// consecutive words: an atomic instruction then covers whole 128-byte lines,
+// where four words per lane spread it over four times as many.
 template <int TM, int TN, int NT, int TROW>
 __device__ __forceinline__ void gemm_tile_atomic_add(const GemmLaunch& g, const uint32_t* tile, int64_t m0,
                                                      int64_t n0, int tid) {
-  constexpr int CPR = TN / 4;
-  constexpr int PER = TM * CPR / NT;
-#pragma unroll
-  for (int k = 0; k < PER; ++k) {
-    const int c = tid + NT * k;
-    const int r = c / CPR;
+  static_assert(NT % TN == 0 && TM * TN % NT == 0, "whole rows per pass");
+  const int c = tid % TN;
+  const int64_t n = n0 + c;
+  if (n >= g.N) return;
+#pragma unroll 4
+  for (int r = tid / TN; r < TM; r += NT / TN) {
     const int64_t m = m0 + r;
-    const int64_t n = n0 + 4 * (c % CPR);
-    if (m >= g.M || n >= g.N) continue;
-    const uint4 a = *(const uint4*)(tile + r * TROW + 4 * (c % CPR));
-    uint32_t* cr = g.c + m * g.ldc + n;
-    atomicAdd(cr, a.x);
-    if (n + 1 < g.N) atomicAdd(cr + 1, a.y);
-    if (n + 2 < g.N) atomicAdd(cr + 2, a.z);
-    if (n + 3 < g.N) atomicAdd(cr + 3, a.w);
+    if (m < g.M) atomicAdd(g.c + m * g.ldc + n, tile[r * TROW + c]);
   }
 }
 
@@ -169,9 +190,11 @@ __device__ __forceinline__ void gemm_tile_atomic_add(const GemmLaunch& g, const 
 // result is stored (launch_ring_gemm).
 // SPLIT: compiled in only for launches with split tiles, so that the
 // whole-tile kernel keeps a compile-time stage origin of 0.
-template <int EPI, int VEC, bool SPLIT>
-__global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
-  __shared__ __attribute__((aligned(1024))) char lds[NSTAGE * STAGE];
+template <class F, int EPI, int VEC, bool SPLIT>
+__global__ __launch_bounds__(F::NT, 2) void ring_gemm_kernel(GemmLaunch g) {
+  constexpr int BM = F::BM, NST = F::NST, OPA = F::OPA, OPB = F::OPB, NL = F::NL, UN = F::UN, KW = F::KW;
+  constexpr int SB = KW * ROWB;                     // a group's bytes of a row from stage to stage
+  __shared__ __attribute__((aligned(1024))) char lds_all[KW * F::GRP];
 
   const int64_t tiles_m = (g.M + BM - 1) / BM;
   const int64_t tiles_n = (g.N + BN - 1) / BN;
@@ -182,34 +205,42 @@ __global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
   const int64_t q = piece ? p / g.split_tiles : 0;
   const int64_t lin = piece ? full + (p - q * g.split_tiles) : xcd_order(blockIdx.x, full);
   const int s0 = piece ? 2 * (int)((int64_t)(total / 2) * q / g.split_k) : 0;
-  const int stages = piece ? 2 * (int)((int64_t)(total / 2) * (q + 1) / g.split_k) - s0 : total;
+  const int stages_all = piece ? 2 * (int)((int64_t)(total / 2) * (q + 1) / g.split_k) - s0 : total;
   const Tile tile = tile_at(lin, tiles_m, tiles_n);
   const int64_t m0 = tile.tm * BM;
   const int64_t n0 = tile.tn * BN;
   const int64_t rows_a = (g.M - m0) < BM ? (g.M - m0) : BM;
   const int64_t rows_b = (g.N - n0) < BN ? (g.N - n0) : BN;
-  // a piece's operands start at its first stage; the ranges end where the
-  // tile's rows end
-  const v4i rsa = make_rsrc(g.a + m0 * g.a_pitch + s0 * ROWB, rows_a * g.a_pitch - s0 * ROWB);
-  const v4i rsb = make_rsrc(g.b + n0 * g.b_pitch + s0 * ROWB, rows_b * g.b_pitch - s0 * ROWB);
-
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wave_all = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int kw = KW > 1 ? wave_all / F::NW : 0;
+  const int wave = wave_all - kw * F::NW;
+  const int stages = __builtin_amdgcn_readfirstlane(stages_all / KW);               // this group's: stage s of it is stage s0 + KW s + kw
+  // a group's operands start at its first stage; the ranges end where the
+  // tile's rows end
+  const int64_t first = (int64_t)(s0 + kw) * ROWB;
+  const v4i rsa = make_rsrc(g.a + m0 * g.a_pitch + first, rows_a * g.a_pitch - first);
+  const v4i rsb = make_rsrc(g.b + n0 * g.b_pitch + first, rows_b * g.b_pitch - first);
+  char* const lds = lds_all + kw * F::GRP;
   const int wm = wave >> 2;
   const int wn = wave & 3;
 
-  // direct loads: wave w fills rows 16 w + 8 q .. +8 (q = 0, 1) of A and of B
-  int voff[4];   // A q0, B q0, A q1, B q1
+  // direct loads: wave w fills rows 16 w + 8 q .. +8 (q = 0, 1) of A and RB w +
+  // 8 q .. +8 (q < RB / 8) of B; load k: A for k = 0 and 2, else B
+  int va[2], vb[F::RB / 8];
 #pragma unroll
   for (int q = 0; q < 2; ++q) {
     const int R = wave * 16 + q * 8 + (lane >> 3);
-    const int c = (lane & 7) ^ ((R >> 1) & 7);
-    voff[2 * q] = R * (int)g.a_pitch + c * 16;
-    voff[2 * q + 1] = R * (int)g.b_pitch + c * 16;
+    va[q] = R * (int)g.a_pitch + ((lane & 7) ^ ((R >> 1) & 7)) * 16;
   }
-  const uint32_t lds_wave =
-      (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds + wave * 16 * ROWB;
+#pragma unroll
+  for (int q = 0; q < F::RB / 8; ++q) {
+    const int R = wave * F::RB + q * 8 + (lane >> 3);
+    vb[q] = R * (int)g.b_pitch + ((lane & 7) ^ ((R >> 1) & 7)) * 16;
+  }
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds;
+  const uint32_t lds_a = lds0 + wave * 16 * ROWB, lds_b = lds0 + NST * OPA + wave * F::RB * ROWB;
 
   // fragment reads: lane reads row (lane % 32) of a 32-row tile, chunk
   // 4 (lane / 32) + t for digit t
@@ -220,7 +251,7 @@ __global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
   for (int t = 0; t < 4; ++t) {
     const int p = ((lane >> 5) * 4 + t) ^ f;
     fo[t] = (wm * 64 + rr) * ROWB + p * 16;
-    fo[4 + t] = NSTAGE * OPS + (wn * 32 + rr) * ROWB + p * 16;
+    fo[4 + t] = NST * OPA + (wn * 32 + rr) * ROWB + p * 16;
   }
 
   v16i acc[2][4];
@@ -233,21 +264,23 @@ __global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
 
   v4i fa[2][2][4], fb[2][4];             // [register set][tile][digit], [register set][digit]
 
-#define MOSAIC_DMA(S, k)                                                                   \
-  dma16(((k) & 1) ? rsb : rsa,                                                            \
-        lds_wave + ((S) & (NSTAGE - 1)) * OPS + ((k) & 1) * NSTAGE * OPS + ((k) >> 1) * 8 * ROWB, voff[k], \
-        (S) * ROWB)
-
-#define MOSAIC_READ(S, SET, idx)                                                           \
+// SO: the stage's byte offset along a row
+#define MOSAIC_DMA(SO, SLOT, k)                                                            \
   do {                                                                                     \
-    const char* base_ = lds + ((S) & (NSTAGE - 1)) * OPS;                                  \
+    if ((k) == 0 || (k) == 2) dma16(rsa, lds_a + (SLOT) * OPA + ((k) / 2) * 8 * ROWB, va[(k) / 2], SO); \
+    else dma16(rsb, lds_b + (SLOT) * OPB + ((k) == 1 ? 0 : (k) - 2) * 8 * ROWB, vb[(k) == 1 ? 0 : (k) - 2],     \
+               SO);                                                                        \
+  } while (0)
+
+#define MOSAIC_READ(SLOT, SET, idx)                                                        \
+  do {                                                                                     \
     if ((idx) < 8) {                                                                       \
       const int i_ = (idx) >> 2, t_ = (idx) & 3;                                           \
-      const uint4 v_ = *(const uint4*)(base_ + i_ * 32 * ROWB + fo[t_]);                   \
+      const uint4 v_ = *(const uint4*)(lds + (SLOT) * OPA + i_ * 32 * ROWB + fo[t_]);      \
       fa[SET][i_][t_] = v4i{(int)v_.x, (int)v_.y, (int)v_.z, (int)v_.w};                   \
     } else {                                                                               \
       const int t_ = (idx) - 8;                                                            \
-      const uint4 v_ = *(const uint4*)(base_ + fo[4 + t_]);                                \
+      const uint4 v_ = *(const uint4*)(lds + (SLOT) * OPB + fo[4 + t_]);                   \
       fb[SET][t_] = v4i{(int)v_.x, (int)v_.y, (int)v_.z, (int)v_.w};                       \
     }                                                                                      \
   } while (0)
@@ -277,104 +310,114 @@ __global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
         __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[SET][i_][a_], fb[SET][b_], acc[i_][a_ + b_], 0, 0, 0); \
   } while (0)
 
-  // group g of a stage: MFMAs 5g .. 5g+4, then direct load g of stage S+4
-  // and (g < 3) fragment reads 4g .. 4g+3 of stage S+1
-#define MOSAIC_STAGE(CUR, NXT, S) MOSAIC_STAGE_IF(CUR, NXT, S, (S) + NSTAGE < stages, (S) + 1 < stages)
-#define MOSAIC_STAGE_IF(CUR, NXT, S, REFILL, NEXT)                                         \
+  // group g of a stage: MFMAs 5g .. 5g+4, then its share of the direct loads
+  // of stage S+NST (one load, or 2, 2, 1, 1 of six) and (g < 3) fragment reads
+  // 4g .. 4g+3 of stage S+1. SLOT and NSLOT: S and S+1 modulo NST.
+#define MOSAIC_STAGE(CUR, NXT, SO, SLOT, NSLOT, REFILL, NEXT)                              \
   do {                                                                                     \
     const bool refill_ = (REFILL);                                                         \
     const bool next_ = (NEXT);                                                             \
     _Pragma("unroll") for (int gq = 0; gq < 4; ++gq) {                                     \
       _Pragma("unroll") for (int u = 0; u < 5; ++u) MOSAIC_MFMA(CUR, gq * 5 + u);          \
       if (refill_) {                                                                       \
-        MOSAIC_DMA((S) + NSTAGE, gq);                                                      \
+        constexpr int k0_[5] = {0, NL / 3, 2 * (NL / 3), NL == 4 ? 3 : 5, NL};             \
+        _Pragma("unroll") for (int k = k0_[gq]; k < k0_[gq + 1]; ++k) MOSAIC_DMA((SO) + NST * SB, SLOT, k); \
       }                                                                                    \
       if (gq < 3 && next_) {                                                               \
-        _Pragma("unroll") for (int r = 0; r < 4; ++r) MOSAIC_READ((S) + 1, NXT, 4 * gq + r); \
+        _Pragma("unroll") for (int r = 0; r < 4; ++r) MOSAIC_READ(NSLOT, NXT, 4 * gq + r); \
       }                                                                                    \
       __builtin_amdgcn_sched_barrier(0);                                                   \
     }                                                                                      \
   } while (0)
 
-  // prologue: stages 0..3 in flight, stage 0 published and read
-  for (int s = 0; s < NSTAGE; ++s)
+  // prologue: stages 0 .. NST-1 in flight, stage 0 published and read
+#pragma unroll
+  for (int s = 0; s < NST; ++s)
     if (s < stages) {
 #pragma unroll
-      for (int k = 0; k < 4; ++k) MOSAIC_DMA(s, k);
+      for (int k = 0; k < NL; ++k) MOSAIC_DMA(s * SB, s, k);
     }
   if (stages > 0) {
-    wait_loads(imin(NSTAGE - 1, stages - 1));
+    wait_loads<NL>(imin(NST - 1, stages - 1));
     __builtin_amdgcn_s_barrier();
 #pragma unroll
     for (int k = 0; k < 12; ++k) MOSAIC_READ(0, 0, k);
   }
 
   // Before stage S: this wave's loads of stage S+1 have landed (loads of up
-  // to stage S+3 issued, at most two later stages in flight) and its reads of
-  // stage S have completed (the pin); the barrier then makes stage S+1
-  // visible to every wave and guarantees nobody still reads stage S's slot,
-  // which stage S's loads refill with stage S+4.
+  // to stage S+NST-1 issued, at most NST-2 later stages in flight) and its
+  // reads of stage S have completed (the pin); the barrier then makes stage
+  // S+1 visible to every wave and guarantees nobody still reads stage S's
+  // slot, which stage S's loads refill with stage S+NST.
   // The steady state, where every stage refills its slot and reads the next
-  // one, runs as a loop without conditions: one basic block per four stages
-  // (slots 0..3 in turn), which the scheduler interleaves freely within the
+  // one, runs as a loop without conditions: one basic block per UN stages
+  // (the slots in turn), which the scheduler interleaves freely within the
   // pinned groups (the server products 1.5-3% faster than with the tests
-  // inside every stage). The last four stages of a multiple of four run as
+  // inside every stage). The last NST stages, when just those remain, run as
   // straight-line code with their waits fixed (bench steps 0.4-0.6% faster
   // than through the general loop, mostly from the short Init X and unmask
-  // products); other remainders, and stage counts below eight, take the
-  // general loop.
-  int it = 0;
-  for (; NSTAGE * it + 2 * NSTAGE <= stages; ++it) {
-    const int s4 = NSTAGE * it;
+  // products); other remainders, and short stage counts, take the general
+  // loop.
+  int s = 0;
+  for (; s + UN + NST <= stages; s += UN) {
+    int so = s * SB;                    // kept a scalar: it must not merge with the vector offsets
+    asm volatile("" : "+s"(so));
 #pragma unroll
-    for (int h = 0; h < NSTAGE; h += 2) {
-      wait_loads(NSTAGE - 2);
+    for (int h = 0; h < UN; h += 2) {
+      wait_vm<NL * (NST - 2)>();
       MOSAIC_PIN(0);
       __builtin_amdgcn_s_barrier();
-      MOSAIC_STAGE_IF(0, 1, s4 + h, true, true);
-      wait_loads(NSTAGE - 2);
+      MOSAIC_STAGE(0, 1, so + h * SB, h % NST, (h + 1) % NST, true, true);
+      wait_vm<NL * (NST - 2)>();
       MOSAIC_PIN(1);
       __builtin_amdgcn_s_barrier();
-      MOSAIC_STAGE_IF(1, 0, s4 + h + 1, true, true);
+      MOSAIC_STAGE(1, 0, so + (h + 1) * SB, (h + 1) % NST, (h + 2) % NST, true, true);
     }
   }
-  int s = NSTAGE * it;
-  if (it > 0 && stages - s == NSTAGE) {
-    // the last four stages when the stage count is a multiple of four: no
-    // refills, the waits shrink as the loads in flight run out
-    wait_loads(2);
-    MOSAIC_PIN(0);
-    __builtin_amdgcn_s_barrier();
-    MOSAIC_STAGE_IF(0, 1, s, false, true);
-    wait_loads(1);
-    MOSAIC_PIN(1);
-    __builtin_amdgcn_s_barrier();
-    MOSAIC_STAGE_IF(1, 0, s + 1, false, true);
-    wait_loads(0);
-    MOSAIC_PIN(0);
-    __builtin_amdgcn_s_barrier();
-    MOSAIC_STAGE_IF(0, 1, s + 2, false, true);
-    MOSAIC_PIN(1);
-    MOSAIC_STAGE_IF(1, 0, s + 3, false, false);
+  if (NST % 2 == 0 && s > 0 && stages - s == NST) {
+    // no refills, the waits shrink as the loads in flight run out
+#pragma unroll
+    for (int h = 0; h < NST; h += 2) {
+      wait_loads<NL>(NST - 2 - h);
+      MOSAIC_PIN(0);
+      __builtin_amdgcn_s_barrier();
+      MOSAIC_STAGE(0, 1, 0, h % NST, (h + 1) % NST, false, true);
+      if (h + 2 < NST) {
+        wait_loads<NL>(NST - 3 - h);
+        MOSAIC_PIN(1);
+        __builtin_amdgcn_s_barrier();
+        MOSAIC_STAGE(1, 0, 0, (h + 1) % NST, (h + 2) % NST, false, true);
+      } else {
+        MOSAIC_PIN(1);
+        MOSAIC_STAGE(1, 0, 0, (h + 1) % NST, (h + 2) % NST, false, false);
+      }
+    }
     s = stages;
   }
-  for (; s < stages; s += 2) {
-    wait_loads(imin(NSTAGE - 2, stages - 2 - s));
+  for (int slot = 0; s + 1 < stages; s += 2) {      // s is a multiple of NST here: slot 0
+    const int slot1 = slot + 1 < NST ? slot + 1 : 0, slot2 = slot1 + 1 < NST ? slot1 + 1 : 0;
+    int so = s * SB;
+    asm volatile("" : "+s"(so));
+    wait_loads<NL>(imin(NST - 2, stages - 2 - s));
     MOSAIC_PIN(0);
     __builtin_amdgcn_s_barrier();
-    MOSAIC_STAGE(0, 1, s);
-    if (s + 2 < stages) wait_loads(imin(NSTAGE - 2, stages - 3 - s));
+    MOSAIC_STAGE(0, 1, so, slot, slot1, s + NST < stages, true);
+    if (s + 2 < stages) wait_loads<NL>(imin(NST - 2, stages - 3 - s));
     MOSAIC_PIN(1);
     if (s + 2 < stages) __builtin_amdgcn_s_barrier();
-    MOSAIC_STAGE(1, 0, s + 1);
+    MOSAIC_STAGE(1, 0, so + SB, slot1, slot2, s + 1 + NST < stages, s + 2 < stages);
+    slot = slot2;
   }
-  __builtin_amdgcn_s_waitcnt(0x0F70);   // no direct load outlives the loop
+  if (KW > 1 && s < stages) {           // an odd count: a group's share of an even one
+    MOSAIC_PIN(0);
+    MOSAIC_STAGE(0, 1, 0, 0, 0, false, false);
+  }
+  wait_vm<0>();                         // no direct load outlives the loop
 #undef MOSAIC_DMA
 #undef MOSAIC_READ
 #undef MOSAIC_PIN
 #undef MOSAIC_MFMA
 #undef MOSAIC_STAGE
-#undef MOSAIC_STAGE_IF
 
   // epilogue: recombine the shift classes and write. Output layout of the
   // 32 x 32 MFMA: register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4,
@@ -386,25 +429,33 @@ __global__ __launch_bounds__(NTHREADS, 1) void ring_gemm_kernel(GemmLaunch g) {
   // wave instruction covers two whole 512-byte tile rows. All loads of the
   // unmask epilogue (Y', K_c, scales) are issued before its first store.
   __builtin_amdgcn_s_barrier();                 // every wave is done reading stage data
-  uint32_t* ctile = (uint32_t*)lds;
+  uint32_t* ctile = (uint32_t*)lds_all;
   constexpr int TROW = BN + 4;
 #pragma unroll
-  for (int i = 0; i < 2; ++i) {
+  for (int k = KW - 1; k >= 0; --k) {           // the last group stores its part, the others add theirs
+    if (kw == k) {
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int r = wm * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      const int c = wn * 32 + (lane & 31);
-      ctile[r * TROW + c] = (uint32_t)acc[i][0][v] + ((uint32_t)acc[i][1][v] << 8) +
-                           ((uint32_t)acc[i][2][v] << 16) + ((uint32_t)acc[i][3][v] << 24);
+      for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int r = wm * 64 + i * 32 + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+          const int c = wn * 32 + (lane & 31);
+          const uint32_t val = (uint32_t)acc[i][0][v] + ((uint32_t)acc[i][1][v] << 8) +
+                               ((uint32_t)acc[i][2][v] << 16) + ((uint32_t)acc[i][3][v] << 24);
+          if (k == KW - 1) ctile[r * TROW + c] = val;
+          else ctile[r * TROW + c] += val;
+        }
+      }
     }
+    __syncthreads();
   }
-  __syncthreads();
-  if (EPI != EPI_UNMASK && piece) gemm_tile_atomic_add<BM, BN, NTHREADS, TROW>(g, ctile, m0, n0, tid);
-  else gemm_tile_epilogue<EPI, VEC, BM, BN, NTHREADS, TROW>(g, ctile, m0, n0, tid);
+  if (EPI != EPI_UNMASK && piece) gemm_tile_atomic_add<BM, BN, F::NT, TROW>(g, ctile, m0, n0, tid);
+  else gemm_tile_epilogue<EPI, VEC, BM, BN, F::NT, TROW>(g, ctile, m0, n0, tid);
 }
 
 // C = 0 over the last split_tiles tiles of the logical order (one workgroup
 // per tile).
+template <int BM>
 __global__ __launch_bounds__(256) void clear_split_tiles_kernel(GemmLaunch g) {
   const int64_t tiles_m = (g.M + BM - 1) / BM;
   const int64_t tiles_n = (g.N + BN - 1) / BN;
@@ -416,74 +467,116 @@ __global__ __launch_bounds__(256) void clear_split_tiles_kernel(GemmLaunch g) {
   }
 }
 
-// Tiles to split and pieces per tile for a launch of `tiles` whole tiles
-// over `cus` compute units. Only the last, partial round of tiles is split,
-// and only when it would leave at least half of the compute units idle: the
-// chip is power-limited on uniform digits, so a last round on three quarters
-// of the units runs at higher clocks, and splitting it measured no faster
-// (2048 x 9728 x 8192: 1.22 ms whole, 1.24-1.26 ms with the last 192 tiles in
-// four pieces). With a round costing one tile's stages plus a fixed cost per
-// workgroup (its prologue and epilogue, taken as 6 stages) and the clear
-// before a store (5 stages), split_k pieces of the tail's tiles take
-// ceil(tail split_k / cus) rounds of stages / split_k + 6; pieces keep at
-// least two stage pairs.
-void choose_split(int64_t tiles, int64_t stages, int64_t cus, bool store, int64_t* split_tiles, int* split_k) {
-  *split_tiles = 0;
-  *split_k = 1;
-  if (cus <= 0) return;
-  const int64_t tail = tiles % cus;
-  if (tail == 0 || 2 * tail >= cus) return;
-  constexpr int64_t kFixed = 6, kClear = 5;
-  int64_t best = stages + kFixed;
-  for (int k : {2, 3, 4, 6, 8}) {
-    if (stages / 2 < 2 * (int64_t)k) break;
-    const int64_t rounds = (tail * k + cus - 1) / cus;
-    const int64_t cost = rounds * (stages / k + kFixed) + (store ? kClear : 0);
-    if (cost < best) {
-      best = cost;
-      *split_k = k;
+// The forms of the kernel and what a product is estimated to take in each,
+// in microseconds on a chip of `cus` compute units (fitted to 65-2048 rows
+// against 4608-14336 columns at 48, 128 and 256 stages; within 10% of nearly
+// all of those). All of it follows from two rates. A compute unit by itself
+// takes 0.58 us for a stage of a 128 x 128 tile; with every unit busy on
+// uniform digits the chip is power-limited to 0.96 us a stage.
+//
+// FORM_128, 128 x 128 tiles: whole rounds at 0.96 us a stage, the last round at
+// what its tiles leave of the power, 7 us a round for the prologue and the
+// epilogue.
+// FORM_128 with its last round split along K (launch_ring_gemm; not for the
+// unmask epilogue, which needs whole products): that round's tiles run as k
+// pieces each, added into C atomically, at 5 us per million words added, and
+// C cleared first for a store. Only a round that would leave at least half of
+// the units idle: a last round on three quarters of them runs at higher
+// clocks, and splitting it measured no faster.
+// FORM_64K, 64 x 128 tiles, two groups of waves splitting the stages: for
+// products of at most one tile per unit. A tile costs a unit 0.45 us a stage,
+// so a short product on few units takes two thirds of FORM_128's time (200 x
+// 4608 x 1536 unmask: 23 against 34 us; 200 x 6144 x 4096: 57 against 80 us
+// whole, 66 split in two).
+// FORM_64, 64 x 128 tiles, two workgroups to a unit: half the work per tile
+// and no common rounds, so products of one and a bit, or two and a bit, rounds
+// of FORM_128 waste less of the last (333 x 14336 x 1536 unmask: 79 against
+// 90 us; 1024 x 6144 x 4096: 197 against 220 us), but 1.5 times the operand
+// traffic, which costs 2-6% where the rounds are full or many (2048 x 6144 x
+// 4096: 382 against 368 us).
+enum GemmForm { FORM_128, FORM_64K, FORM_64 };
+
+struct GemmPlan {
+  GemmForm form;
+  int64_t split_tiles;
+  int split_k;
+};
+
+GemmPlan choose_plan(int64_t M, int64_t N, int64_t stages, int64_t cus, EpilogueKind epi) {
+  const int64_t tn = (N + BN - 1) / BN;
+  const int64_t t128 = ((M + 127) / 128) * tn, t64 = ((M + 63) / 64) * tn;
+  const double S = (double)stages, full = (double)(t128 / cus);
+  const int64_t tail = t128 % cus;
+  const double whole = full * (0.96 * S + 7.0) + 2.0;
+  const auto round = [&](double share) { return (share * 0.96 > 0.58 ? share * 0.96 : 0.58) * S + 7.0; };
+
+  GemmPlan plan{FORM_128, 0, 1};
+  double best = whole + (tail > 0 ? round((double)tail / (double)cus) : 0.0);
+  if (epi != EPI_UNMASK && tail > 0 && 2 * tail < cus) {
+    for (int k : {2, 3, 4, 6, 8}) {
+      if (stages / 2 < 2 * (int64_t)k) break;            // a piece keeps at least two stage pairs
+      const double rounds = (double)((tail * k + cus - 1) / cus);
+      const double words = (double)tail * k * 128.0 * (double)(M < 128 ? M : 128);
+      const double work = 0.58 * S / k * rounds;
+      const double read = (double)tail * (double)tn / (double)t128 * BN * ROWB * S / 5.2e6;   // B once
+      const double cost = whole + (work > read ? work : read) + 7.0 * rounds + 5e-6 * words +
+                          (epi == EPI_STORE ? 4.0 : 0.0);
+      if (cost < best) {
+        best = cost;
+        plan = GemmPlan{FORM_128, tail, k};
+      }
     }
   }
-  if (*split_k > 1) *split_tiles = tail;
+  const double half = (double)((t64 + cus - 1) / cus);   // tiles of 64 rows per unit, rounded up
+  const double power = 0.55 * (double)t64 / (double)cus * S, reach = 0.38 * half * S;
+  const double c64 = t64 <= cus ? 0.45 * S + 3.0 : (power > reach ? power : reach) + 8.0;
+  if (c64 < best) plan = GemmPlan{t64 <= cus ? FORM_64K : FORM_64, 0, 1};
+  return plan;
+}
+
+template <class F, int EPI, bool SPLIT>
+void launch_form_epi(const GemmLaunch& g, dim3 grid, bool vec, hipStream_t s) {
+  if (vec) hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, 1, SPLIT>), grid, dim3(F::NT), 0, s, g);
+  else hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, 0, SPLIT>), grid, dim3(F::NT), 0, s, g);
+}
+
+// g.split_tiles and g.split_k are set.
+template <class F>
+hipError_t launch_form(const GemmLaunch& g, EpilogueKind epi, hipStream_t s) {
+  const int64_t tiles = ((g.M + F::BM - 1) / F::BM) * ((g.N + BN - 1) / BN);
+  const dim3 grid((unsigned)(tiles + g.split_tiles * (g.split_k - 1)));
+  const bool vec = gemm_epilogue_vectorizable(g, epi);
+  if constexpr (F::BM == 128) {          // the form that splits
+    if (g.split_tiles > 0) {
+      if (epi == EPI_STORE) {
+        hipLaunchKernelGGL(clear_split_tiles_kernel<F::BM>, dim3((unsigned)g.split_tiles), dim3(256), 0, s, g);
+        launch_form_epi<F, EPI_STORE, true>(g, grid, vec, s);
+      } else {
+        launch_form_epi<F, EPI_ACCUM, true>(g, grid, vec, s);
+      }
+      return hipGetLastError();
+    }
+  }
+  if (epi == EPI_STORE) launch_form_epi<F, EPI_STORE, false>(g, grid, vec, s);
+  else if (epi == EPI_ACCUM) launch_form_epi<F, EPI_ACCUM, false>(g, grid, vec, s);
+  else launch_form_epi<F, EPI_UNMASK, false>(g, grid, vec, s);
+  return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_ring_gemm(const GemmLaunch& g, EpilogueKind epi, hipStream_t s) {
   if (g.M <= SKINNY_MAX_M) return launch_ring_gemm_skinny(g, epi, s);
-  const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
-  if (tiles == 0) return hipSuccess;
+  if (g.N <= 0) return hipSuccess;
+  GemmPlan p = choose_plan(g.M, g.N, g.Kp / BK, compute_units(), epi);
   GemmLaunch gs = g;
-  gs.split_tiles = 0;
-  gs.split_k = 1;
-  if (epi != EPI_UNMASK)   // the unmask epilogue needs the whole product of a tile
-    choose_split(tiles, g.Kp / BK, compute_units(), epi == EPI_STORE, &gs.split_tiles, &gs.split_k);
-  if (gs.split_tiles > 0 && epi == EPI_STORE)
-    hipLaunchKernelGGL(clear_split_tiles_kernel, dim3((unsigned)gs.split_tiles), dim3(256), 0, s, gs);
-  const dim3 grid((unsigned)(tiles + gs.split_tiles * (gs.split_k - 1)));
-  const bool vec = gemm_epilogue_vectorizable(g, epi);
-  const bool split = gs.split_tiles > 0;
-  if (epi == EPI_STORE) {
-    if (split) {
-      if (vec) hipLaunchKernelGGL((ring_gemm_kernel<EPI_STORE, 1, true>), grid, dim3(NTHREADS), 0, s, gs);
-      else hipLaunchKernelGGL((ring_gemm_kernel<EPI_STORE, 0, true>), grid, dim3(NTHREADS), 0, s, gs);
-    } else {
-      if (vec) hipLaunchKernelGGL((ring_gemm_kernel<EPI_STORE, 1, false>), grid, dim3(NTHREADS), 0, s, gs);
-      else hipLaunchKernelGGL((ring_gemm_kernel<EPI_STORE, 0, false>), grid, dim3(NTHREADS), 0, s, gs);
-    }
-  } else if (epi == EPI_ACCUM) {
-    if (split) {
-      if (vec) hipLaunchKernelGGL((ring_gemm_kernel<EPI_ACCUM, 1, true>), grid, dim3(NTHREADS), 0, s, gs);
-      else hipLaunchKernelGGL((ring_gemm_kernel<EPI_ACCUM, 0, true>), grid, dim3(NTHREADS), 0, s, gs);
-    } else {
-      if (vec) hipLaunchKernelGGL((ring_gemm_kernel<EPI_ACCUM, 1, false>), grid, dim3(NTHREADS), 0, s, gs);
-      else hipLaunchKernelGGL((ring_gemm_kernel<EPI_ACCUM, 0, false>), grid, dim3(NTHREADS), 0, s, gs);
-    }
-  } else {
-    if (vec) hipLaunchKernelGGL((ring_gemm_kernel<EPI_UNMASK, 1, false>), grid, dim3(NTHREADS), 0, s, gs);
-    else hipLaunchKernelGGL((ring_gemm_kernel<EPI_UNMASK, 0, false>), grid, dim3(NTHREADS), 0, s, gs);
+  gs.split_tiles = p.split_tiles;
+  gs.split_k = p.split_k;
+  switch (p.form) {
+    case FORM_64K: return launch_form<Form<1, 2, 3>>(gs, epi, s);
+    case FORM_64: return launch_form<Form<1, 1, 3>>(gs, epi, s);
+    default: return launch_form<Form<2, 1, 4>>(gs, epi, s);
   }
-  return hipGetLastError();
 }
 
 }  // namespace mosaic
