@@ -5,6 +5,7 @@
 #include <atomic>
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -166,10 +167,10 @@ __device__ __forceinline__ void gemm_epilogue(const GemmLaunch& g, int64_t m, in
   }
 }
 
-// True if the tile epilogue may use 16-byte accesses for every operand:
+// True if every operand of the tile epilogue is aligned for 16-byte accesses:
 // N % 4 == 0 (so a 4-column chunk is wholly inside or outside the matrix),
 // 16-byte aligned base pointers and row pitches that are multiples of 4.
-inline bool gemm_epilogue_vectorizable(const GemmLaunch& g, EpilogueKind epi) {
+inline bool gemm_epilogue_aligned(const GemmLaunch& g, EpilogueKind epi) {
   auto ok = [](const void* p, int64_t ld) { return p == nullptr || ((((uintptr_t)p) & 15) == 0 && (ld & 3) == 0); };
   if (g.N % 4 != 0) return false;
   if (epi == EPI_STORE || epi == EPI_ACCUM) return ok(g.c, g.ldc);
@@ -179,96 +180,106 @@ inline bool gemm_epilogue_vectorizable(const GemmLaunch& g, EpilogueKind epi) {
 
 // Epilogue of a TM x TN output tile held in LDS (row pitch TROW words) by a
 // workgroup of NT threads: chunks of 4 consecutive columns, thread t taking
-// chunks t, t + NT, .... VEC (see gemm_epilogue_vectorizable): 16-byte
-// accesses, and the unmask inputs of all of a thread's chunks are loaded
-// first, from addresses clamped into the matrix so that the loads need no
-// branches (values of chunks outside the matrix are discarded). Otherwise one
-// word at a time through gemm_epilogue.
-template <int EPI, int VEC, int TM, int TN, int NT, int TROW>
+// chunks t, t + NT, ... with 16-byte accesses; the unmask inputs of all of a
+// thread's chunks are loaded first, from addresses clamped into the matrix so
+// that the loads need no branches (values of chunks outside the matrix are
+// discarded). AL (see gemm_epilogue_aligned): the accesses are aligned.
+// Otherwise they are 16 bytes wide at word alignment, and the chunk that holds
+// the last columns of an N that is not a multiple of 4 goes word by word
+// (every chunk did so before, four words per lane and a load's latency per
+// word: 59 against 38 us for the unmask of 333 x 5003 at rank 1536).
+template <int EPI, bool AL, int TM, int TN, int NT, int TROW>
 __device__ __forceinline__ void gemm_tile_epilogue(const GemmLaunch& g, const uint32_t* tile, int64_t m0,
                                                    int64_t n0, int tid) {
+  using W4 = std::conditional_t<AL, u32x4, u32x4_any>;
+  using F4 = std::conditional_t<AL, f32x4, f32x4_any>;
   constexpr int CPR = TN / 4;                     // chunks per tile row
   constexpr int PER = TM * CPR / NT;              // chunks per thread
   static_assert(TM * CPR % NT == 0, "tile must split evenly");
-  if (!VEC) {
-    for (int k = 0; k < PER; ++k) {
-      const int c = tid + NT * k;
-      const int r = c / CPR;
-      const int64_t m = m0 + r;
-      const int64_t n = n0 + 4 * (c % CPR);
+  // row m and column n of chunk k; whole: all four columns in the matrix
+  const auto at = [&](int k, int& r, int64_t& m, int64_t& n) {
+    const int c = tid + NT * k;
+    r = c / CPR;
+    m = m0 + r;
+    n = n0 + 4 * (c % CPR);
+  };
+  // the chunk of the ragged last columns (or a matrix of fewer than 4)
+  const auto ragged = [&](int r, int64_t m, int64_t n) {
+    if constexpr (!AL) {
+#pragma unroll
       for (int e = 0; e < 4; ++e)
-        if (m < g.M && n + e < g.N) gemm_epilogue<EPI>(g, m, n + e, tile[r * TROW + 4 * (c % CPR) + e]);
+        if (n + e < g.N) gemm_epilogue<EPI>(g, m, n + e, tile[r * TROW + (int)(n - n0) + e]);
     }
-    return;
-  }
+  };
+  int r;
+  int64_t m, n;
   if (EPI == EPI_STORE) {
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int c = tid + NT * k;
-      const int r = c / CPR;
-      const int64_t m = m0 + r;
-      const int64_t n = n0 + 4 * (c % CPR);
-      if (m < g.M && n < g.N)
-        *(uint4*)(g.c + m * g.ldc + n) = *(const uint4*)(tile + r * TROW + 4 * (c % CPR));
+      at(k, r, m, n);
+      if (m >= g.M || n >= g.N) continue;
+      if (!AL && n + 4 > g.N) ragged(r, m, n);
+      else *(W4*)(g.c + m * g.ldc + n) = *(const u32x4*)(tile + r * TROW + (int)(n - n0));
     }
     return;
   }
+  const int64_t last = AL || g.N >= 4 ? g.N - 4 : 0;   // clamp of a chunk's first column
+  const bool wide = AL || g.N >= 4;                     // clamped chunks lie inside the row
   if (EPI == EPI_ACCUM) {
-    uint4 cv[PER];                                  // every c chunk is read before the first store
+    u32x4 cv[PER];                                  // every c chunk is read before the first store
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int c = tid + NT * k;
-      const int64_t m = min(m0 + c / CPR, g.M - 1);
-      const int64_t n = min(n0 + 4 * (c % CPR), g.N - 4);
-      cv[k] = *(const uint4*)(g.c + m * g.ldc + n);
+      at(k, r, m, n);
+      if (wide) cv[k] = *(const W4*)(g.c + min(m, g.M - 1) * g.ldc + min(n, last));
     }
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-      const int c = tid + NT * k;
-      const int r = c / CPR;
-      const int64_t m = m0 + r;
-      const int64_t n = n0 + 4 * (c % CPR);
+      at(k, r, m, n);
       if (m >= g.M || n >= g.N) continue;
-      const uint4 a = *(const uint4*)(tile + r * TROW + 4 * (c % CPR));
-      *(uint4*)(g.c + m * g.ldc + n) = make_uint4(cv[k].x + a.x, cv[k].y + a.y, cv[k].z + a.z, cv[k].w + a.w);
+      if (!AL && n + 4 > g.N) ragged(r, m, n);
+      else *(W4*)(g.c + m * g.ldc + n) = cv[k] + *(const u32x4*)(tile + r * TROW + (int)(n - n0));
     }
     return;
   }
   const bool dq = g.y_f32 != nullptr;
-  uint4 ymv[PER], kcv[PER];
-  float4 scv[PER], bv[PER];
+  u32x4 ymv[PER], kcv[PER];
+  f32x4 scv[PER], bv[PER];
   float srv[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int c = tid + NT * k;
-    const int64_t m = min(m0 + c / CPR, g.M - 1);
-    const int64_t n = min(n0 + 4 * (c % CPR), g.N - 4);
-    ymv[k] = *(const uint4*)(g.ym + m * g.ldy + n);
-    kcv[k] = g.kc != nullptr ? *(const uint4*)(g.kc + m * g.ldk + n) : make_uint4(0u, 0u, 0u, 0u);
+    at(k, r, m, n);
+    m = min(m, g.M - 1);
+    n = min(n, last);
+    kcv[k] = u32x4{0u, 0u, 0u, 0u};
+    if (!wide) continue;
+    ymv[k] = *(const W4*)(g.ym + m * g.ldy + n);
+    if (g.kc != nullptr) kcv[k] = *(const W4*)(g.kc + m * g.ldk + n);
     if (dq) {
-      scv[k] = *(const float4*)(g.s_cols + n);
+      scv[k] = *(const F4*)(g.s_cols + n);
       srv[k] = g.s_rows[m];
-      bv[k] = g.bias != nullptr ? *(const float4*)(g.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
+      bv[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (g.bias != nullptr) bv[k] = *(const F4*)(g.bias + n);
     }
   }
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
-    const int c = tid + NT * k;
-    const int r = c / CPR;
-    const int64_t m = m0 + r;
-    const int64_t n = n0 + 4 * (c % CPR);
+    at(k, r, m, n);
     if (m >= g.M || n >= g.N) continue;
-    const uint4 a = *(const uint4*)(tile + r * TROW + 4 * (c % CPR));
-    const uint32_t o0 = ymv[k].x - kcv[k].x - a.x, o1 = ymv[k].y - kcv[k].y - a.y;
-    const uint32_t o2 = ymv[k].z - kcv[k].z - a.z, o3 = ymv[k].w - kcv[k].w - a.w;
-    if (g.y != nullptr) *(int4*)(g.y + m * g.ldo + n) = make_int4((int)o0, (int)o1, (int)o2, (int)o3);
+    if (!AL && n + 4 > g.N) {
+      ragged(r, m, n);
+      continue;
+    }
+    const u32x4 o = ymv[k] - kcv[k] - *(const u32x4*)(tile + r * TROW + (int)(n - n0));
+    if (g.y != nullptr) *(W4*)((uint32_t*)g.y + m * g.ldo + n) = o;
     if (dq) {
-      float4 f = make_float4((float)(int32_t)o0 * srv[k] * scv[k].x, (float)(int32_t)o1 * srv[k] * scv[k].y,
-                             (float)(int32_t)o2 * srv[k] * scv[k].z, (float)(int32_t)o3 * srv[k] * scv[k].w);
-      if (g.bias != nullptr)
-        f = make_float4(__fadd_rn(f.x, bv[k].x), __fadd_rn(f.y, bv[k].y), __fadd_rn(f.z, bv[k].z),
-                        __fadd_rn(f.w, bv[k].w));
-      *(float4*)(g.y_f32 + m * g.ldf + n) = f;
+      f32x4 f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+#pragma clang fp contract(off)
+        f[e] = (float)(int32_t)o[e] * srv[k] * scv[k][e];
+        if (g.bias != nullptr) f[e] = f[e] + bv[k][e];   // a rounding of its own
+      }
+      *(F4*)(g.y_f32 + m * g.ldf + n) = f;
     }
   }
 }

@@ -190,7 +190,7 @@ __device__ __forceinline__ void gemm_tile_atomic_add(const GemmLaunch& g, const 
 // result is stored (launch_ring_gemm).
 // SPLIT: compiled in only for launches with split tiles, so that the
 // whole-tile kernel keeps a compile-time stage origin of 0.
-template <class F, int EPI, int VEC, bool SPLIT>
+template <class F, int EPI, bool AL, bool SPLIT>
 __global__ __launch_bounds__(F::NT, 2) void ring_gemm_kernel(GemmLaunch g) {
   constexpr int BM = F::BM, NST = F::NST, OPA = F::OPA, OPB = F::OPB, NL = F::NL, UN = F::UN, KW = F::KW;
   constexpr int SB = KW * ROWB;                     // a group's bytes of a row from stage to stage
@@ -450,7 +450,7 @@ __global__ __launch_bounds__(F::NT, 2) void ring_gemm_kernel(GemmLaunch g) {
     __syncthreads();
   }
   if (EPI != EPI_UNMASK && piece) gemm_tile_atomic_add<BM, BN, F::NT, TROW>(g, ctile, m0, n0, tid);
-  else gemm_tile_epilogue<EPI, VEC, BM, BN, F::NT, TROW>(g, ctile, m0, n0, tid);
+  else gemm_tile_epilogue<EPI, AL, BM, BN, F::NT, TROW>(g, ctile, m0, n0, tid);
 }
 
 // C = 0 over the last split_tiles tiles of the logical order (one workgroup
@@ -535,9 +535,9 @@ GemmPlan choose_plan(int64_t M, int64_t N, int64_t stages, int64_t cus, Epilogue
 }
 
 template <class F, int EPI, bool SPLIT>
-void launch_form_epi(const GemmLaunch& g, dim3 grid, bool vec, hipStream_t s) {
-  if (vec) hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, 1, SPLIT>), grid, dim3(F::NT), 0, s, g);
-  else hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, 0, SPLIT>), grid, dim3(F::NT), 0, s, g);
+void launch_form_epi(const GemmLaunch& g, dim3 grid, bool aligned, hipStream_t s) {
+  if (aligned) hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, true, SPLIT>), grid, dim3(F::NT), 0, s, g);
+  else hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, false, SPLIT>), grid, dim3(F::NT), 0, s, g);
 }
 
 // g.split_tiles and g.split_k are set.
@@ -545,21 +545,21 @@ template <class F>
 hipError_t launch_form(const GemmLaunch& g, EpilogueKind epi, hipStream_t s) {
   const int64_t tiles = ((g.M + F::BM - 1) / F::BM) * ((g.N + BN - 1) / BN);
   const dim3 grid((unsigned)(tiles + g.split_tiles * (g.split_k - 1)));
-  const bool vec = gemm_epilogue_vectorizable(g, epi);
+  const bool aligned = gemm_epilogue_aligned(g, epi);
   if constexpr (F::BM == 128) {          // the form that splits
     if (g.split_tiles > 0) {
       if (epi == EPI_STORE) {
         hipLaunchKernelGGL(clear_split_tiles_kernel<F::BM>, dim3((unsigned)g.split_tiles), dim3(256), 0, s, g);
-        launch_form_epi<F, EPI_STORE, true>(g, grid, vec, s);
+        launch_form_epi<F, EPI_STORE, true>(g, grid, aligned, s);
       } else {
-        launch_form_epi<F, EPI_ACCUM, true>(g, grid, vec, s);
+        launch_form_epi<F, EPI_ACCUM, true>(g, grid, aligned, s);
       }
       return hipGetLastError();
     }
   }
-  if (epi == EPI_STORE) launch_form_epi<F, EPI_STORE, false>(g, grid, vec, s);
-  else if (epi == EPI_ACCUM) launch_form_epi<F, EPI_ACCUM, false>(g, grid, vec, s);
-  else launch_form_epi<F, EPI_UNMASK, false>(g, grid, vec, s);
+  if (epi == EPI_STORE) launch_form_epi<F, EPI_STORE, false>(g, grid, aligned, s);
+  else if (epi == EPI_ACCUM) launch_form_epi<F, EPI_ACCUM, false>(g, grid, aligned, s);
+  else launch_form_epi<F, EPI_UNMASK, false>(g, grid, aligned, s);
   return hipGetLastError();
 }
 
