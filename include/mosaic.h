@@ -310,6 +310,34 @@ mosaic_status mosaic_sparse_gather_cols(int64_t M, int64_t N, const int64_t* row
                                         int64_t ldc, int32_t subtract, const float* s_rows, const float* s_cols,
                                         const float* bias, float* y_f32, int64_t ldf, void* stream);
 
+/* The two gathers above over up to 4 matrices in one call, as for the levels
+ * of a nested mask: c +-= the sum over the terms, the same words as the
+ * single calls one after the other. A term of the first is (rng, rcols, d,
+ * ldd) of mosaic_sparse_stream_gather_rows; a term of the second adds to the
+ * operands of mosaic_sparse_gather_cols the number of columns of its P (the
+ * column indices are below it; ldd >= cols). nterms >= 1 for the second. */
+typedef struct mosaic_stream_term {
+  mosaic_rng rng;
+  int64_t rcols;
+  const uint32_t* d;
+  int64_t ldd;
+} mosaic_stream_term;
+typedef struct mosaic_sparse_term {
+  const int64_t* row_ptr;
+  const int32_t* col_idx;
+  const uint32_t* values;
+  int64_t cols;
+  const uint32_t* d;
+  int64_t ldd;
+} mosaic_sparse_term;
+mosaic_status mosaic_sparse_stream_gather_rows_terms(const mosaic_stream_term* terms, int32_t nterms, int64_t rows,
+                                                     int64_t ncols, uint32_t* c, int64_t ldc, int32_t subtract,
+                                                     void* stream);
+mosaic_status mosaic_sparse_gather_cols_terms(const mosaic_sparse_term* terms, int32_t nterms, int64_t M, int64_t N,
+                                              uint32_t* c, int64_t ldc, int32_t subtract, const float* s_rows,
+                                              const float* s_cols, const float* bias, float* y_f32, int64_t ldf,
+                                              void* stream);
+
 /* Integrity check (Freivalds' test; Appendix "Computational integrity" and
  * online step 4 of the Section 4.2 protocol box): the client compares two
  * short products that agree whenever the server's product was computed

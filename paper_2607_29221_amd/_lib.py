@@ -35,6 +35,15 @@ class MosaicRng(ctypes.Structure):
     ]
 
 
+class MosaicStreamTerm(ctypes.Structure):
+    _fields_ = [("rng", MosaicRng), ("rcols", c_i64), ("d", c_ptr), ("ldd", c_i64)]
+
+
+class MosaicSparseTerm(ctypes.Structure):
+    _fields_ = [("row_ptr", c_ptr), ("col_idx", c_ptr), ("values", c_ptr), ("cols", c_i64), ("d", c_ptr),
+                ("ldd", c_i64)]
+
+
 # name -> argument types (all return mosaic_status as int32 unless listed)
 _SIGNATURES = {
     "mosaic_abi_version": ([], c_i32),
@@ -65,6 +74,10 @@ _SIGNATURES = {
                                           c_i32, c_ptr], c_i32),
     "mosaic_sparse_gather_cols": ([c_i64, c_i64, c_ptr, c_ptr, c_ptr, c_ptr, c_i64, c_ptr, c_i64, c_i32,
                                    c_ptr, c_ptr, c_ptr, c_ptr, c_i64, c_ptr], c_i32),
+    "mosaic_sparse_stream_gather_rows_terms": ([ctypes.POINTER(MosaicStreamTerm), c_i32, c_i64, c_i64, c_ptr, c_i64,
+                                                c_i32, c_ptr], c_i32),
+    "mosaic_sparse_gather_cols_terms": ([ctypes.POINTER(MosaicSparseTerm), c_i32, c_i64, c_i64, c_ptr, c_i64, c_i32,
+                                         c_ptr, c_ptr, c_ptr, c_ptr, c_i64, c_ptr], c_i32),
     "mosaic_hadamard_rotate": ([c_ptr, c_i64, c_ptr, c_i64, c_i64, c_i64, c_i64, c_ptr, c_i32, c_ptr], c_i32),
     "mosaic_hadamard28_rotate": ([c_ptr, c_i64, c_ptr, c_i64, c_i64, c_i64, c_ptr, c_i32, c_ptr], c_i32),
     "mosaic_probe_mfma_i8": ([c_i32, c_i64, c_ptr, ctypes.POINTER(c_i64), c_ptr], c_i32),

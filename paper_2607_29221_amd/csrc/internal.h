@@ -51,6 +51,29 @@ hipError_t launch_sparse_gather_cols(int64_t M, int64_t N, const int64_t* row_pt
                                      const uint32_t* values, const uint32_t* d, int64_t ldd, uint32_t* c,
                                      int64_t ldc, int subtract, const Dequant& dq, hipStream_t s);
 
+// The gathers over several matrices at once (sparse_terms.hip).
+constexpr int MAX_TERMS = 4;
+struct StreamTerm {
+  RngArgs r;
+  int64_t rcols;
+  const uint32_t* d;
+  int64_t ldd;
+};
+struct SparseTerm {
+  const int64_t* row_ptr;
+  const int32_t* col_idx;
+  const uint32_t* values;
+  const uint32_t* d;
+  int64_t ldd, cols;
+};
+// One matrix, its row's entries staged in chunks: rows of any length.
+hipError_t launch_gather_stream_single(const RngArgs& r, int64_t rows, int64_t rcols, const uint32_t* d, int64_t ldd,
+                                       int64_t ncols, uint32_t* c, int64_t ldc, int subtract, hipStream_t s);
+hipError_t launch_sparse_stream_gather_rows_terms(const StreamTerm* terms, int nterms, int64_t rows, int64_t ncols,
+                                                  uint32_t* c, int64_t ldc, int subtract, hipStream_t s);
+hipError_t launch_sparse_gather_cols_terms(const SparseTerm* terms, int nterms, int64_t M, int64_t N, uint32_t* c,
+                                           int64_t ldc, int subtract, const Dequant& dq, hipStream_t s);
+
 // Fixed-row-weight (WEIGHT) streams: at most WEIGHT_MAX_COLS columns (the
 // row's permutation lives in LDS) and, where a row is staged whole in LDS,
 // WEIGHT_MAX_T entries.

@@ -13,7 +13,7 @@ from __future__ import annotations
 
 import ctypes
 from dataclasses import dataclass
-from typing import List, Optional, Sequence
+from typing import List, Optional, Sequence, Tuple
 
 import torch
 
@@ -360,6 +360,46 @@ def mosaic_sparse_gather_cols(p: SparseRows, d: torch.Tensor, M: int, c: torch.T
                                                  _ptr(bias), _ptr(y_f32), y_f32.stride(0) if y_f32 is not None else 0,
                                                  _stream()),
            "mosaic_sparse_gather_cols")
+
+
+def mosaic_sparse_stream_gather_rows_terms(terms: Sequence[Tuple[_lib.MosaicRng, int, torch.Tensor]], rows: int,
+                                           ncols: int, c: torch.Tensor, subtract: bool = False) -> None:
+    """c[i, :ncols] +-= the sum over the terms (r, rcols, d) of
+    mosaic_sparse_stream_gather_rows, in one call."""
+    _need(c, rows, ncols, "c", _INT, optional=False)
+    arr = (_lib.MosaicStreamTerm * max(1, len(terms)))()
+    for t, (r, rcols, d) in zip(arr, terms):
+        _need(d, rcols, ncols, "d", _INT, optional=False)
+        t.rng, t.rcols, t.d, t.ldd = r, rcols, d.data_ptr(), d.stride(0)
+    _check(_lib.load().mosaic_sparse_stream_gather_rows_terms(arr, len(terms), rows, ncols, c.data_ptr(), c.stride(0),
+                                                              1 if subtract else 0, _stream()),
+           "mosaic_sparse_stream_gather_rows_terms")
+
+
+def mosaic_sparse_gather_cols_terms(terms: Sequence[Tuple[SparseRows, torch.Tensor]], M: int, c: torch.Tensor,
+                                    subtract: bool = False, y_f32: Optional[torch.Tensor] = None,
+                                    s_rows: Optional[torch.Tensor] = None, s_cols: Optional[torch.Tensor] = None,
+                                    bias: Optional[torch.Tensor] = None) -> None:
+    """c[m, n] +-= the sum over the terms (p, d) of mosaic_sparse_gather_cols,
+    in one call; y_f32 as there."""
+    N = terms[0][0].rows
+    _need(c, M, N, "c", _INT, optional=False)
+    _need(y_f32, M, N, "y_f32", (torch.float32,))
+    if y_f32 is not None:
+        _need(s_rows, 1, M, "s_rows", (torch.float32,), optional=False)
+        _need(s_cols, 1, N, "s_cols", (torch.float32,), optional=False)
+    _need(bias, 1, N, "bias", (torch.float32,))
+    arr = (_lib.MosaicSparseTerm * len(terms))()
+    for t, (p, d) in zip(arr, terms):
+        if p.rows != N:
+            raise ValueError("the terms' matrices have different row counts")
+        _need(d, M, p.cols, "d", _INT, optional=False)
+        t.row_ptr, t.col_idx, t.values = p.row_ptr.data_ptr(), p.col_idx.data_ptr(), p.values.data_ptr()
+        t.cols, t.d, t.ldd = p.cols, d.data_ptr(), max(d.stride(0), p.cols)
+    _check(_lib.load().mosaic_sparse_gather_cols_terms(arr, len(terms), M, N, c.data_ptr(), c.stride(0),
+                                                       1 if subtract else 0, _ptr(s_rows), _ptr(s_cols), _ptr(bias),
+                                                       _ptr(y_f32), y_f32.stride(0) if y_f32 is not None else 0,
+                                                       _stream()), "mosaic_sparse_gather_cols_terms")
 
 
 def mosaic_count_mismatches(a: torch.Tensor, b: torch.Tensor, count: torch.Tensor) -> None:

@@ -305,9 +305,12 @@ def init_x(w: MaskedWeight, M: int, call_id: int, buf: CallBuffers) -> None:
     # a few nonzeros per token, drawn inside the gather) against
     # D_i = [(N_1..N_i)^T | J_i^T]
     m.mosaic_masked_matmul(buf.rho[0].whole(w.Rd), w.Bx_dense.whole(w.Rd), M, w.K + w.N, w.Rd, buf.UK)
-    for lv, D in w.D.items():
-        m.mosaic_sparse_stream_gather_rows(_lpn_rng(p, lv + 1, s, STREAM_T + lv + 1, call_id),
-                                           M, r[lv - 1], D, w.K + w.N, buf.UK)
+    terms = [(_lpn_rng(p, lv + 1, s, STREAM_T + lv + 1, call_id), r[lv - 1], D) for lv, D in w.D.items()]
+    if len(terms) == 1:
+        m.mosaic_sparse_stream_gather_rows(terms[0][0], M, terms[0][1], terms[0][2], w.K + w.N, buf.UK)
+        return
+    for k in range(0, len(terms), 4):
+        m.mosaic_sparse_stream_gather_rows_terms(terms[k: k + 4], M, w.K + w.N, buf.UK)
 
 
 def mask(w: MaskedWeight, A: torch.Tensor, call_id: int, buf: CallBuffers) -> None:
@@ -347,13 +350,13 @@ def unmask(w: MaskedWeight, M: int, buf: CallBuffers, y_f32: Optional[torch.Tens
                         M, w.N, qw, **kw)
     if not sparse:
         return
-    gathers = [(slot, lv) for slot, lv in enumerate(w.slot_levels) if lv in w.S]
-    for k, (slot, lv) in enumerate(gathers):
-        c0 = w.q_cols[slot]
-        last = k == len(gathers) - 1         # the last gather also writes the dequantised output
-        m.mosaic_sparse_gather_cols(w.S[lv], buf.YQ[:, c0: c0 + r[lv - 1]], M, buf.Y, subtract=True,
-                                    y_f32=y_f32 if last else None, s_rows=s_rows if last else None,
-                                    s_cols=s_cols if last else None, bias=bias if last else None)
+    gathers = [(w.S[lv], buf.YQ[:, w.q_cols[slot]: w.q_cols[slot] + r[lv - 1]])
+               for slot, lv in enumerate(w.slot_levels) if lv in w.S]
+    for k in range(0, len(gathers), 4):
+        last = k + 4 >= len(gathers)         # the last gather also writes the dequantised output
+        m.mosaic_sparse_gather_cols_terms(gathers[k: k + 4], M, buf.Y, subtract=True,
+                                          y_f32=y_f32 if last else None, s_rows=s_rows if last else None,
+                                          s_cols=s_cols if last else None, bias=bias if last else None)
     if y_f32 is not None and not gathers:    # dequantise the finished result (no product term)
         m.mosaic_unmask(buf.Y, None, None, None, M, w.N, 0, s_rows=s_rows, s_cols=s_cols, y_f32=y_f32, bias=bias)
 
