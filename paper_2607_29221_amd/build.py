@@ -1,7 +1,9 @@
 """Build libmosaic.so in-tree with hipcc for gfx950.
 
 Every HIP source under csrc/ is compiled to an object file under _build/ and
-linked into paper_2607_29221_amd/libmosaic.so. Run ``python -m
+linked into paper_2607_29221_amd/libmosaic.so; csrc/binding.cpp, the Python
+binding's native marshalling, is compiled by the host compiler into
+paper_2607_29221_amd/_binding.so. Run ``python -m
 paper_2607_29221_amd.build`` (or ``__graft_entry__.build()``). Beside the
 library the build writes libmosaic.so.sources, a digest of every file it was
 built from (csrc/, include/) and of the compiler flags; the loader refuses a
@@ -13,6 +15,7 @@ import hashlib
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -20,6 +23,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libmosaic.so")
+BINDING = os.path.join(HERE, "_binding.so")
 STAMP = LIB + ".sources"
 INCLUDE = os.path.join(ROOT, "include")
 ARCH = os.environ.get("MOSAIC_OFFLOAD_ARCH", "gfx950")
@@ -57,11 +61,27 @@ def _compile(src: str) -> str:
     return obj
 
 
+def _build_binding() -> None:
+    import torch
+    root = os.path.dirname(torch.__file__)
+    tmp = BINDING + ".tmp"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}",
+           os.path.join(CSRC, "binding.cpp"), "-o", tmp, f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError(f"compiling the binding failed:\n{res.stdout}\n{res.stderr}")
+    os.replace(tmp, BINDING)
+
+
 def build(verbose: bool = False) -> str:
     digest = source_digest()
     os.makedirs(BUILD, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES) + 1)) as ex:
+        binding = ex.submit(_build_binding)
         objs = list(ex.map(_compile, SOURCES))
+        binding.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp] + objs
     res = subprocess.run(cmd, capture_output=True, text=True)

@@ -3,7 +3,10 @@
 Each function has the name of the ABI entry point it calls and only marshals
 arguments: torch tensors (device memory, on the current HIP stream) become
 pointers, leading dimensions and sizes. All arithmetic runs in the HIP
-kernels of libmosaic.so.
+kernels of libmosaic.so. The functions of an online call hand their arguments
+to _binding.so first (csrc/binding.cpp), which checks and converts a
+well-formed call natively; it declines any other, and the Python code below
+then handles it or says what is wrong with it.
 
 Digit-layout matrices are ``Digits`` views: an int8 tensor of shape
 (rows, pitch) plus a column offset (a multiple of 64), so several factors can
@@ -35,6 +38,25 @@ class MosaicError(RuntimeError):
 def _check(status: int, name: str) -> None:
     if status != 0:
         raise MosaicError(status, name)
+
+
+# Entry points that _binding.so calls, in the order it expects.
+_BOUND = ("mosaic_sample", "mosaic_mask", "mosaic_masked_matmul", "mosaic_integrity_check", "mosaic_unmask",
+          "mosaic_unmask_words", "mosaic_rotate_quantize_mask", "mosaic_sparse_stream_gather_rows_terms",
+          "mosaic_sparse_gather_cols_terms", "mosaic_hadamard_rotate", "mosaic_quantize_rows")
+_b = None
+
+
+def _native():
+    """The native marshalling, bound to the loaded library on first use."""
+    global _b
+    if _b is None:
+        lib = _lib.load()
+        from . import _binding
+        _binding.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND),
+                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+        _b = _binding
+    return _b
 
 
 def _stream() -> int:
@@ -149,6 +171,9 @@ def mosaic_dgauss_thresholds(sigma: float, bound: int) -> List[int]:
 
 def mosaic_sample(r: _lib.MosaicRng, rows: int, cols: int, out: Optional[torch.Tensor] = None,
                   out_dig: Optional[Digits] = None) -> None:
+    st = (_b or _native()).sample(r, rows, cols, out, out_dig)
+    if st is not None:
+        return _check(st, "mosaic_sample")
     _need(out, rows, cols, "out", _INT)
     _need_dig(out_dig, rows, cols, "out_dig")
     ldo = out.stride(0) if out is not None else 0
@@ -162,6 +187,9 @@ def mosaic_mask(x: Optional[torch.Tensor], u: Optional[torch.Tensor], noise: Opt
                 out_dig: Optional[Digits] = None, x_transposed: bool = False) -> None:
     """out = x + u + noise (mod 2^32). ``x_transposed`` reads x[j, i] for
     element (i, j) (x then has shape (cols, rows))."""
+    st = (_b or _native()).mask(x, u, noise, rows, cols, out, out_dig, x_transposed)
+    if st is not None:
+        return _check(st, "mosaic_mask")
     if x is not None:
         if x.dtype not in _TORCH_DT or not x.is_cuda or x.dim() != 2:
             raise ValueError("x must be an int8/int16/int32 device matrix")
@@ -185,6 +213,9 @@ def mosaic_mask(x: Optional[torch.Tensor], u: Optional[torch.Tensor], noise: Opt
 
 def mosaic_masked_matmul(a: Digits, b: Digits, M: int, N: int, K: int, c: torch.Tensor) -> None:
     """c[:M, :N] = A B^T over Z_{2^32} (c is an int32 tensor holding ring words)."""
+    st = (_b or _native()).masked_matmul(a, b, M, N, K, c)
+    if st is not None:
+        return _check(st, "mosaic_masked_matmul")
     _need_dig(a, M, K, "a", optional=False)
     _need_dig(b, N, K, "b", optional=False)
     _need(c, M, N, "c", _INT, optional=False)
@@ -208,6 +239,9 @@ def mosaic_integrity_check(ct: Digits, a: Digits, v: Digits, yq: torch.Tensor, t
                            d: torch.Tensor, count: torch.Tensor) -> None:
     """d = c^T A'^T - V [Y' | Q]^T (t x M) and count[0] = its nonzero entries,
     with [Y' | Q] given as the ring words of yq's first NR columns."""
+    st = (_b or _native()).integrity_check(ct, a, v, yq, t, M, K, NR, d, count)
+    if st is not None:
+        return _check(st, "mosaic_integrity_check")
     _need_dig(ct, t, K, "ct", optional=False)
     _need_dig(a, M, K, "a", optional=False)
     _need_dig(v, t, NR, "v", optional=False)
@@ -224,6 +258,9 @@ def mosaic_unmask(ym: torch.Tensor, kc: Optional[torch.Tensor], q: Optional[Digi
                   M: int, N: int, R: int, y: Optional[torch.Tensor] = None,
                   s_rows: Optional[torch.Tensor] = None, s_cols: Optional[torch.Tensor] = None,
                   y_f32: Optional[torch.Tensor] = None, bias: Optional[torch.Tensor] = None) -> None:
+    st = (_b or _native()).unmask(ym, kc, q, l, M, N, R, y, s_rows, s_cols, y_f32, bias)
+    if st is not None:
+        return _check(st, "mosaic_unmask")
     _need(ym, M, N, "ym", _INT, optional=False)
     _need(kc, M, N, "kc", _INT)
     if R > 0:
@@ -249,6 +286,9 @@ def mosaic_unmask_words(ym: torch.Tensor, kc: Optional[torch.Tensor], q: Optiona
                         y_f32: Optional[torch.Tensor] = None, bias: Optional[torch.Tensor] = None) -> None:
     """mosaic_unmask with q (M x R) as ring words, e.g. the Q columns of the
     server's [Y' | Q]; at most 16 rows."""
+    st = (_b or _native()).unmask_words(ym, kc, q, l, M, N, R, y, s_rows, s_cols, y_f32, bias)
+    if st is not None:
+        return _check(st, "mosaic_unmask_words")
     _need(ym, M, N, "ym", _INT, optional=False)
     _need(kc, M, N, "kc", _INT)
     if R > 0:
@@ -276,6 +316,9 @@ def mosaic_rotate_quantize_mask(x: torch.Tensor, qmax: int, out_dig: Digits, blo
                                 scale: Optional[torch.Tensor] = None) -> None:
     """Fused rotate + quantise + mask of Pi_Sec-Linear's input: digits of
     round(R x / s) + u + noise for every row of x, and the row scales."""
+    st = (_b or _native()).rotate_quantize_mask(x, qmax, out_dig, block, signs, u, noise, scale)
+    if st is not None:
+        return _check(st, "mosaic_rotate_quantize_mask")
     rows, n = x.shape
     _need(x, rows, n, "x", (torch.float32,), optional=False)
     _need_dig(out_dig, rows, n, "out_dig", optional=False)
@@ -333,6 +376,9 @@ def mosaic_sparse_stream_gather_rows(r: _lib.MosaicRng, rows: int, rcols: int, d
                                      c: torch.Tensor, subtract: bool = False) -> None:
     """c[i, :ncols] +-= sum_j P[i, j] d[j, :ncols], P the rows x rcols SPARSE
     stream matrix of ``r`` (drawn inside the call)."""
+    st = (_b or _native()).stream_terms([(r, rcols, d)], rows, ncols, c, subtract)
+    if st is not None:
+        return _check(st, "mosaic_sparse_stream_gather_rows")
     _need(d, rcols, ncols, "d", _INT, optional=False)
     _need(c, rows, ncols, "c", _INT, optional=False)
     _check(_lib.load().mosaic_sparse_stream_gather_rows(ctypes.byref(r), rows, rcols, d.data_ptr(), d.stride(0), ncols,
@@ -366,6 +412,9 @@ def mosaic_sparse_stream_gather_rows_terms(terms: Sequence[Tuple[_lib.MosaicRng,
                                            ncols: int, c: torch.Tensor, subtract: bool = False) -> None:
     """c[i, :ncols] +-= the sum over the terms (r, rcols, d) of
     mosaic_sparse_stream_gather_rows, in one call."""
+    st = (_b or _native()).stream_terms(terms, rows, ncols, c, subtract)
+    if st is not None:
+        return _check(st, "mosaic_sparse_stream_gather_rows_terms")
     _need(c, rows, ncols, "c", _INT, optional=False)
     arr = (_lib.MosaicStreamTerm * max(1, len(terms)))()
     for t, (r, rcols, d) in zip(arr, terms):
@@ -382,6 +431,9 @@ def mosaic_sparse_gather_cols_terms(terms: Sequence[Tuple[SparseRows, torch.Tens
                                     bias: Optional[torch.Tensor] = None) -> None:
     """c[m, n] +-= the sum over the terms (p, d) of mosaic_sparse_gather_cols,
     in one call; y_f32 as there."""
+    st = (_b or _native()).cols_terms(terms, M, c, subtract, y_f32, s_rows, s_cols, bias)
+    if st is not None:
+        return _check(st, "mosaic_sparse_gather_cols_terms")
     N = terms[0][0].rows
     _need(c, M, N, "c", _INT, optional=False)
     _need(y_f32, M, N, "y_f32", (torch.float32,))
@@ -421,6 +473,9 @@ def mosaic_sample_signs(r: _lib.MosaicRng, n: int, out: torch.Tensor) -> None:
 
 def mosaic_hadamard_rotate(x: torch.Tensor, y: torch.Tensor, block: Optional[int] = None,
                            signs: Optional[torch.Tensor] = None, inverse: bool = False) -> None:
+    st = (_b or _native()).hadamard_rotate(x, y, block, signs, inverse)
+    if st is not None:
+        return _check(st, "mosaic_hadamard_rotate")
     rows, n = x.shape
     _need(x, rows, n, "x", (torch.float32,), optional=False)
     _need(y, rows, n, "y", (torch.float32,), optional=False)
@@ -443,6 +498,9 @@ def mosaic_hadamard28_rotate(x: torch.Tensor, y: torch.Tensor, signs: Optional[t
 
 def mosaic_quantize_rows(x: torch.Tensor, qmax: int, q: Optional[torch.Tensor] = None,
                          q_dig: Optional[Digits] = None, scale: Optional[torch.Tensor] = None) -> None:
+    st = (_b or _native()).quantize_rows(x, qmax, q, q_dig, scale)
+    if st is not None:
+        return _check(st, "mosaic_quantize_rows")
     rows, n = x.shape
     _need(x, rows, n, "x", (torch.float32,), optional=False)
     _need(q, rows, n, "q", _INT)

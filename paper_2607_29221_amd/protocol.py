@@ -306,9 +306,6 @@ def init_x(w: MaskedWeight, M: int, call_id: int, buf: CallBuffers) -> None:
     # D_i = [(N_1..N_i)^T | J_i^T]
     m.mosaic_masked_matmul(buf.rho[0].whole(w.Rd), w.Bx_dense.whole(w.Rd), M, w.K + w.N, w.Rd, buf.UK)
     terms = [(_lpn_rng(p, lv + 1, s, STREAM_T + lv + 1, call_id), r[lv - 1], D) for lv, D in w.D.items()]
-    if len(terms) == 1:
-        m.mosaic_sparse_stream_gather_rows(terms[0][0], M, terms[0][1], terms[0][2], w.K + w.N, buf.UK)
-        return
     for k in range(0, len(terms), 4):
         m.mosaic_sparse_stream_gather_rows_terms(terms[k: k + 4], M, w.K + w.N, buf.UK)
 

@@ -1,0 +1,57 @@
+"""The native marshalling declines what is not a well-formed call, and the
+Python code then says what is wrong with it (no GPU needed: host tensors are
+never well-formed arguments, and nothing is launched)."""
+import pytest
+import torch
+
+from paper_2607_29221_amd import mosaic as m
+from paper_2607_29221_amd.mosaic import Digits
+
+
+def _i32(*shape):
+    return torch.zeros(shape, dtype=torch.int32)
+
+
+def _dig(rows, cols):
+    return Digits.empty(rows, cols, device="cpu")
+
+
+CALLS = {
+    "sample": lambda: m.mosaic_sample(m.rng(1, 2, 3, m.DIST_UNIFORM), 4, 8, out=_i32(4, 8)),
+    "mask": lambda: m.mosaic_mask(_i32(4, 8), None, None, 4, 8, out=_i32(4, 8)),
+    "masked_matmul": lambda: m.mosaic_masked_matmul(_dig(2, 64), _dig(3, 64), 2, 3, 64, _i32(2, 3)),
+    "integrity_check": lambda: m.mosaic_integrity_check(_dig(2, 64), _dig(3, 64), _dig(2, 64), _i32(3, 64), 2, 3, 64,
+                                                        64, _i32(2, 3), torch.zeros(1, dtype=torch.int64)),
+    "unmask": lambda: m.mosaic_unmask(_i32(2, 3), None, _dig(2, 64), _dig(3, 64), 2, 3, 64, y=_i32(2, 3)),
+    "unmask_words": lambda: m.mosaic_unmask_words(_i32(2, 3), None, _i32(2, 64), _dig(3, 64), 2, 3, 64, y=_i32(2, 3)),
+    "rotate_quantize_mask": lambda: m.mosaic_rotate_quantize_mask(torch.zeros(2, 1024), 127, _dig(2, 1024),
+                                                                  scale=torch.zeros(2)),
+    "hadamard_rotate": lambda: m.mosaic_hadamard_rotate(torch.zeros(2, 64), torch.zeros(2, 64)),
+    "quantize_rows": lambda: m.mosaic_quantize_rows(torch.zeros(2, 64), 127, q=_i32(2, 64)),
+    "stream_gather": lambda: m.mosaic_sparse_stream_gather_rows(m.rng(1, 2, 3, m.DIST_SPARSE), 2, 8, _i32(8, 4), 4,
+                                                                _i32(2, 4)),
+    "stream_terms": lambda: m.mosaic_sparse_stream_gather_rows_terms([(m.rng(1, 2, 3, m.DIST_SPARSE), 8, _i32(8, 4))],
+                                                                     2, 4, _i32(2, 4)),
+}
+
+
+@pytest.mark.parametrize("name", list(CALLS))
+def test_host_tensors_are_refused(name):
+    with pytest.raises(ValueError):
+        CALLS[name]()
+
+
+def test_native_functions_decline():
+    b = m._native()
+    r = m.rng(1, 2, 3, m.DIST_UNIFORM)
+    assert b.sample(r, 4, 8, _i32(4, 8), None) is None              # host memory
+    assert b.sample(b"short", 4, 8, None, None) is None             # not an rng
+    assert b.sample(r, 0, 8, None, None) is None                    # empty
+    assert b.sample(r, 4.0, 8, None, None) is None                  # not a size
+    assert b.sample(r, 1 << 70, 8, None, None) is None              # does not fit
+    assert b.sample(r, 4, 8) is None                                # too few arguments
+    assert b.masked_matmul(None, None, 2, 3, 64, None) is None
+    assert b.masked_matmul(object(), 5, 2, 3, 64, "c") is None
+    assert b.stream_terms([], 2, 4, None, False) is None
+    with pytest.raises(TypeError):
+        b.bind((1, 2), None, None)
