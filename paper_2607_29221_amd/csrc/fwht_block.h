@@ -10,9 +10,9 @@
 //  * the stages on index bits 2-7, the lane bits of t, exchange values
 //    between the lanes of a wave (DPP, swizzle and lane-swap instructions);
 //  * the stages on the wave bits of t (index bits 8 .. 1 + log2 T: 8-9 for
-//    256 threads, 8-10 for 512; present for b >= 512) go
+//    256 threads, 8-11 for 1024; present for b >= 512) go
 //    through LDS in one pass: the block is written out, each thread gathers
-//    2, 4 or 8 elements that differ in those bits, runs the stages and writes
+//    2 to 16 elements that differ in those bits, runs the stages and writes
 //    them back, and the result is read back in the load layout (register r
 //    of thread t holds element 4 (t + T (r / 4)) + r % 4), unscaled.
 // LDS addresses are padded by one word per 32 (idx + idx / 32), which makes
@@ -25,8 +25,7 @@ namespace mosaic {
 
 __host__ __device__ constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v >> 1); }
 
-// TMAX: most threads per block transform (256, or 512 for kernels that want
-// more waves per block).
+// TMAX: most threads per block transform (see fwht_tmax).
 template <int LOGB, int TMAX = 256>
 struct FwhtShape {
   static constexpr int B = 1 << LOGB;
@@ -46,12 +45,15 @@ struct FwhtShape {
 
 // Threads per block transform in the rotation kernel and the fused input
 // kernels (they must agree: the thread count fixes which butterfly stages
-// run in registers, lanes or LDS, and so the rounding). 512 for b = 8192,
-// where the block's LDS (33 KiB) admits four workgroups per compute unit:
-// eight waves per workgroup instead of four double the waves resident and
-// halve each thread's share of the block (4096 x 8192 rotation: 45.3 against
-// 47.0 us); 256 otherwise.
-__host__ __device__ constexpr int fwht_tmax(int logb) { return logb == 13 ? 512 : 256; }
+// run in registers, lanes or LDS, and so the rounding): 256 while the block's
+// LDS admits enough workgroups of them, then more, so that the few workgroups
+// that fit still fill the compute unit's wave slots and a thread's share of
+// the block stays small. b = 8192 (33 KiB, four workgroups): 512, 45.3 against
+// 47.0 us for 4096 rows. b = 16384 (66 KiB, two): 1024; with 256 a thread held
+// 64 values, the fused kernel's noise table went to scratch memory and its
+// 2048 rows took 303 us, now 86; the rotation 57 -> 48-51 us (512 threads: 90
+// and 52). b = 32768 (132 KiB, one): 1024, 2048 rows 159 -> 106-112 us (512: 127).
+__host__ __device__ constexpr int fwht_tmax(int logb) { return logb >= 14 ? 1024 : logb == 13 ? 512 : 256; }
 
 // One thread's share of a block, as registers.
 template <int LOGB, int TMAX = 256>

@@ -15,14 +15,15 @@
 // of each code is replaced by a product with the reciprocal of the scale
 // wherever that provably rounds to the same integer (quant_codes4).
 //
-// Rows that fit in registers with room to spare (n = 8192 with b = 8192,
-// 4096 or 1024, and 16384 with b = 16384) run in one launch
-// (rqm_row_kernel: 12 bytes per element; 8-28% faster than two launches
-// there). A 28672-float row held whole needs about 180 registers per lane:
-// the few workgroups that fit made it 47% slower, so it takes the two
-// launches. Otherwise two launches, one
-// workgroup per row each, with only the block transform's scratch in LDS
-// (so occupancy is that of the plain rotation): the first
+// Rows that fit in registers with room to spare (up to 12288 entries for the
+// block counts listed at the dispatch, and 16384 with b = 16384) run in one
+// launch (rqm_row_kernel: 12 bytes per element, one set of butterflies and one
+// launch fewer; 2048 rows of 1024 / 5120 / 12288 entries 8 / 25 / 60 us against
+// 16 / 36 / 75, four rows of 2048 5 us against 8). A 28672-float row held whole
+// needs about 180 registers per lane: the few workgroups that fit made it 47%
+// slower. Otherwise two launches, one workgroup per row each, with only the
+// block transform's scratch in LDS (so occupancy is that of the plain
+// rotation): the first
 // rotates the row block by block and keeps only max |y| (written to
 // scale[row]); the second rotates again -- the butterflies are cheap next to
 // the memory traffic -- quantises with s = max / q_max, adds u and the noise
@@ -250,16 +251,21 @@ hipError_t launch_rotate_quantize_mask(const float* x, int64_t ldx, int64_t rows
                                        hipStream_t s) {
   if (rows == 0) return hipSuccess;
   if (signs != nullptr && u != nullptr) {
-    // rows that fit in registers: one launch
-    const int64_t nb = n >> log2_block;
-    if (log2_block == 13 && nb == 1)
-      return launch_rqm_row<13, 1, 1>(x, ldx, rows, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s);
-    if (log2_block == 12 && nb == 2)
-      return launch_rqm_row<12, 2, 2>(x, ldx, rows, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s);
-    if (log2_block == 10 && nb == 8)
-      return launch_rqm_row<10, 8, 4>(x, ldx, rows, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s);
-    if (log2_block == 14 && nb == 1)
-      return launch_rqm_row<14, 1, 1>(x, ldx, rows, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s);
+    // rows that fit in registers, for the block counts that a length whose
+    // largest power of two is b has: one launch (ROW: log2 b, blocks, blocks per
+    // LDS pass: all of them while their LDS leaves six waves per SIMD, else one).
+    // Not 7 blocks of 2048: with 14 groups of noise in straight-line code the
+    // compiler copied the noise parameters to scratch memory (138 us for 2048
+    // rows against 90 in two launches).
+#define ROW(LB, NB, G)                  \
+  if (log2_block == LB && n >> LB == NB) \
+  return launch_rqm_row<LB, NB, G>(x, ldx, rows, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s)
+    ROW(10, 1, 1); ROW(10, 3, 3); ROW(10, 5, 5); ROW(10, 7, 7); ROW(10, 8, 4); ROW(10, 9, 3); ROW(10, 11, 1);
+    ROW(11, 1, 1); ROW(11, 3, 3); ROW(11, 5, 1);
+    ROW(12, 1, 1); ROW(12, 2, 2); ROW(12, 3, 1);
+    ROW(13, 1, 1);
+    ROW(14, 1, 1);
+#undef ROW
   }
   switch (log2_block) {
     case 10: return launch_rqm<10>(x, ldx, rows, n, signs, qmax, u, ldu, noise, out_dig, pitch, scale, s);
