@@ -142,7 +142,23 @@ bool current_stream(void** s) {
   return true;
 }
 
-int64_t truth(PyObject* o) { return PyObject_IsTrue(o) == 1; }
+bool truth(PyObject* o, int32_t* v) {
+  *v = PyObject_IsTrue(o);
+  if (*v < 0) PyErr_Clear();
+  return *v >= 0;
+}
+
+// The status of an ABI call, made without the interpreter lock: a launch may
+// wait for room in its stream's queue, and other threads go on meanwhile (the
+// caller's frame holds the arguments).
+template <class Call>
+PyObject* status(Call call) {
+  int32_t st;
+  Py_BEGIN_ALLOW_THREADS
+  st = call();
+  Py_END_ALLOW_THREADS
+  return PyLong_FromLong(st);
+}
 
 #define NEED(cond) \
   if (!(cond)) Py_RETURN_NONE
@@ -167,7 +183,9 @@ FUNCTION(sample, 5) {
   void* s;
   NEED(r.get(a[0], false) && size(a[1], &rows) && size(a[2], &cols));
   NEED(matrix(a[3], rows, cols, at::kInt, true, &out) && digits(a[4], rows, cols, true, &dig) && current_stream(&s));
-  return PyLong_FromLong(abi.sample(r.p(), rows, cols, (uint32_t*)out.p, out.ld, (int8_t*)dig.p, dig.ld, s));
+  return status([&] {
+    return abi.sample(r.p(), rows, cols, (uint32_t*)out.p, out.ld, (int8_t*)dig.p, dig.ld, s);
+  });
 }
 
 // (x, u, noise, rows, cols, out, out_dig, x_transposed)
@@ -182,7 +200,8 @@ FUNCTION(mask, 8) {
   if (a[0] != Py_None) {
     const at::Tensor* x = plain(a[0]);
     NEED(x != nullptr && x->dim() == 2);
-    const bool turned = truth(a[7]) != 0;
+    int32_t turned;
+    NEED(truth(a[7], &turned));
     switch (x->scalar_type()) {
       case at::kChar: dt = MOSAIC_I8; break;
       case at::kShort: dt = MOSAIC_I16; break;
@@ -197,8 +216,10 @@ FUNCTION(mask, 8) {
   }
   NEED(matrix(a[1], rows, cols, at::kInt, true, &u) && matrix(a[5], rows, cols, at::kInt, true, &out) &&
        digits(a[6], rows, cols, true, &dig) && current_stream(&s));
-  return PyLong_FromLong(abi.mask(xp, dt, rs, cs, (const uint32_t*)u.p, u.ld, noise.p(), rows, cols, (uint32_t*)out.p,
-                                  out.ld, (int8_t*)dig.p, dig.ld, s));
+  return status([&] {
+    return abi.mask(xp, dt, rs, cs, (const uint32_t*)u.p, u.ld, noise.p(), rows, cols, (uint32_t*)out.p, out.ld,
+                    (int8_t*)dig.p, dig.ld, s);
+  });
 }
 
 // (a, b, M, N, K, c)
@@ -209,8 +230,9 @@ FUNCTION(masked_matmul, 6) {
   NEED(size(a[2], &M) && size(a[3], &N) && size(a[4], &K));
   NEED(digits(a[0], M, K, false, &x) && digits(a[1], N, K, false, &y) && matrix(a[5], M, N, at::kInt, false, &c) &&
        current_stream(&s));
-  return PyLong_FromLong(abi.masked_matmul((const int8_t*)x.p, x.ld, (const int8_t*)y.p, y.ld, M, N, K,
-                                           (uint32_t*)c.p, c.ld, s));
+  return status([&] {
+    return abi.masked_matmul((const int8_t*)x.p, x.ld, (const int8_t*)y.p, y.ld, M, N, K, (uint32_t*)c.p, c.ld, s);
+  });
 }
 
 // (ct, a, v, yq, t, M, K, NR, d, count)
@@ -222,9 +244,10 @@ FUNCTION(integrity_check, 10) {
   NEED(digits(a[0], t, K, false, &ct) && digits(a[1], M, K, false, &x) && digits(a[2], t, NR, false, &v) &&
        matrix(a[3], M, NR, at::kInt, false, &yq) && matrix(a[8], t, M, at::kInt, false, &d) &&
        vec(a[9], 1, at::kLong, false, &count) && current_stream(&s));
-  return PyLong_FromLong(abi.integrity_check((const int8_t*)ct.p, ct.ld, (const int8_t*)x.p, x.ld, (const int8_t*)v.p,
-                                             v.ld, (const uint32_t*)yq.p, yq.ld, t, M, K, NR, (uint32_t*)d.p, d.ld,
-                                             (int64_t*)count.p, s));
+  return status([&] {
+    return abi.integrity_check((const int8_t*)ct.p, ct.ld, (const int8_t*)x.p, x.ld, (const int8_t*)v.p, v.ld,
+                               (const uint32_t*)yq.p, yq.ld, t, M, K, NR, (uint32_t*)d.p, d.ld, (int64_t*)count.p, s);
+  });
 }
 
 // Outputs of the unmask calls: y, s_rows, s_cols, y_f32, bias.
@@ -246,10 +269,11 @@ FUNCTION(unmask, 12) {
   NEED(size(a[4], &M) && size(a[5], &N) && size(a[6], &R));
   NEED(matrix(a[0], M, N, at::kInt, false, &ym) && matrix(a[1], M, N, at::kInt, true, &kc) &&
        digits(a[2], M, R, false, &q) && digits(a[3], N, R, false, &l) && o.get(a + 7, M, N) && current_stream(&s));
-  return PyLong_FromLong(abi.unmask((const uint32_t*)ym.p, ym.ld, (const uint32_t*)kc.p, kc.ld, (const int8_t*)q.p,
-                                    q.ld, (const int8_t*)l.p, l.ld, M, N, R, (int32_t*)o.y.p, o.y.ld,
-                                    (const float*)o.sr.p, (const float*)o.sc.p, (const float*)o.bias.p, (float*)o.f.p,
-                                    o.f.ld, s));
+  return status([&] {
+    return abi.unmask((const uint32_t*)ym.p, ym.ld, (const uint32_t*)kc.p, kc.ld, (const int8_t*)q.p, q.ld,
+                      (const int8_t*)l.p, l.ld, M, N, R, (int32_t*)o.y.p, o.y.ld, (const float*)o.sr.p,
+                      (const float*)o.sc.p, (const float*)o.bias.p, (float*)o.f.p, o.f.ld, s);
+  });
 }
 
 // the same with q as ring words
@@ -262,10 +286,11 @@ FUNCTION(unmask_words, 12) {
   NEED(matrix(a[0], M, N, at::kInt, false, &ym) && matrix(a[1], M, N, at::kInt, true, &kc) &&
        matrix(a[2], M, R, at::kInt, false, &q) && digits(a[3], N, R, false, &l) && o.get(a + 7, M, N) &&
        current_stream(&s));
-  return PyLong_FromLong(abi.unmask_words((const uint32_t*)ym.p, ym.ld, (const uint32_t*)kc.p, kc.ld,
-                                          (const uint32_t*)q.p, q.ld, (const int8_t*)l.p, l.ld, M, N, R,
-                                          (int32_t*)o.y.p, o.y.ld, (const float*)o.sr.p, (const float*)o.sc.p,
-                                          (const float*)o.bias.p, (float*)o.f.p, o.f.ld, s));
+  return status([&] {
+    return abi.unmask_words((const uint32_t*)ym.p, ym.ld, (const uint32_t*)kc.p, kc.ld, (const uint32_t*)q.p, q.ld,
+                            (const int8_t*)l.p, l.ld, M, N, R, (int32_t*)o.y.p, o.y.ld, (const float*)o.sr.p,
+                            (const float*)o.sc.p, (const float*)o.bias.p, (float*)o.f.p, o.f.ld, s);
+  });
 }
 
 // rows and columns of a float matrix that a pass reads whole
@@ -289,22 +314,27 @@ FUNCTION(rotate_quantize_mask, 8) {
   NEED(digits(a[2], rows, n, false, &dig) && vec(a[4], n, at::kChar, true, &signs) &&
        matrix(a[5], rows, n, at::kInt, true, &u) && noise.get(a[6], true) && vec(a[7], rows, at::kFloat, true, &scale) &&
        current_stream(&s));
-  return PyLong_FromLong(abi.rotate_quantize_mask((const float*)x.p, x.ld, rows, n, block, (const int8_t*)signs.p,
-                                                  (int32_t)qmax, (const uint32_t*)u.p, u.ld, noise.p(), (int8_t*)dig.p,
-                                                  dig.ld, (float*)scale.p, s));
+  return status([&] {
+    return abi.rotate_quantize_mask((const float*)x.p, x.ld, rows, n, block, (const int8_t*)signs.p, (int32_t)qmax,
+                                    (const uint32_t*)u.p, u.ld, noise.p(), (int8_t*)dig.p, dig.ld, (float*)scale.p, s);
+  });
 }
 
 // (x, y, block, signs, inverse)
 FUNCTION(hadamard_rotate, 5) {
   int64_t rows, n, block;
+  int32_t inverse;
   Mat x, y, signs;
   void* s;
   NEED(whole(a[0], &x, &rows, &n));
   block = n;
   NEED(a[2] == Py_None || integer(a[2], &block));
-  NEED(matrix(a[1], rows, n, at::kFloat, false, &y) && vec(a[3], n, at::kChar, true, &signs) && current_stream(&s));
-  return PyLong_FromLong(abi.hadamard_rotate((const float*)x.p, x.ld, (float*)y.p, y.ld, rows, n, block,
-                                             (const int8_t*)signs.p, (int32_t)truth(a[4]), s));
+  NEED(matrix(a[1], rows, n, at::kFloat, false, &y) && vec(a[3], n, at::kChar, true, &signs) &&
+       truth(a[4], &inverse) && current_stream(&s));
+  return status([&] {
+    return abi.hadamard_rotate((const float*)x.p, x.ld, (float*)y.p, y.ld, rows, n, block, (const int8_t*)signs.p,
+                               inverse, s);
+  });
 }
 
 // (x, qmax, q, q_dig, scale)
@@ -315,8 +345,10 @@ FUNCTION(quantize_rows, 5) {
   NEED(whole(a[0], &x, &rows, &n) && integer(a[1], &qmax) && qmax <= INT32_MAX && qmax >= INT32_MIN);
   NEED(matrix(a[2], rows, n, at::kInt, true, &q) && digits(a[3], rows, n, true, &dig) &&
        vec(a[4], rows, at::kFloat, true, &scale) && current_stream(&s));
-  return PyLong_FromLong(abi.quantize_rows((const float*)x.p, x.ld, rows, n, (int32_t)qmax, (int32_t*)q.p, q.ld,
-                                           (int8_t*)dig.p, dig.ld, (float*)scale.p, s));
+  return status([&] {
+    return abi.quantize_rows((const float*)x.p, x.ld, rows, n, (int32_t)qmax, (int32_t*)q.p, q.ld, (int8_t*)dig.p,
+                             dig.ld, (float*)scale.p, s);
+  });
 }
 
 constexpr int kMaxTerms = 4;
@@ -324,6 +356,7 @@ constexpr int kMaxTerms = 4;
 // (terms, rows, ncols, c, subtract); a term is a tuple (r, rcols, d)
 FUNCTION(stream_terms, 5) {
   int64_t rows, ncols;
+  int32_t subtract;
   Mat c;
   void* s;
   NEED(PyList_CheckExact(a[0]) && size(a[1], &rows) && size(a[2], &ncols) &&
@@ -340,8 +373,10 @@ FUNCTION(stream_terms, 5) {
          size(PyTuple_GET_ITEM(t, 1), &rcols) && matrix(PyTuple_GET_ITEM(t, 2), rcols, ncols, at::kInt, false, &d));
     terms[l] = mosaic_stream_term{*r.p(), rcols, (const uint32_t*)d.p, d.ld};
   }
-  NEED(current_stream(&s));
-  return PyLong_FromLong(abi.stream_terms(terms, (int32_t)n, rows, ncols, (uint32_t*)c.p, c.ld, (int32_t)truth(a[4]), s));
+  NEED(truth(a[4], &subtract) && current_stream(&s));
+  return status([&] {
+    return abi.stream_terms(terms, (int32_t)n, rows, ncols, (uint32_t*)c.p, c.ld, subtract, s);
+  });
 }
 
 bool attr_ptr(PyObject* o, PyObject* name, at::ScalarType dt, const void** p) {
@@ -366,6 +401,7 @@ bool attr_size(PyObject* o, PyObject* name, int64_t* n) {
 // (SparseRows, d)
 FUNCTION(cols_terms, 8) {
   int64_t M, N = 0;
+  int32_t subtract;
   void* s;
   NEED(PyList_CheckExact(a[0]) && size(a[1], &M));
   const Py_ssize_t n = PyList_GET_SIZE(a[0]);
@@ -388,10 +424,11 @@ FUNCTION(cols_terms, 8) {
   Mat c, f, sr, sc, bias;
   NEED(matrix(a[2], M, N, at::kInt, false, &c) && matrix(a[4], M, N, at::kFloat, true, &f) &&
        vec(a[5], M, at::kFloat, !f.given(), &sr) && vec(a[6], N, at::kFloat, !f.given(), &sc) &&
-       vec(a[7], N, at::kFloat, true, &bias) && current_stream(&s));
-  return PyLong_FromLong(abi.cols_terms(terms, (int32_t)n, M, N, (uint32_t*)c.p, c.ld, (int32_t)truth(a[3]),
-                                        (const float*)sr.p, (const float*)sc.p, (const float*)bias.p, (float*)f.p,
-                                        f.ld, s));
+       vec(a[7], N, at::kFloat, true, &bias) && truth(a[3], &subtract) && current_stream(&s));
+  return status([&] {
+    return abi.cols_terms(terms, (int32_t)n, M, N, (uint32_t*)c.p, c.ld, subtract, (const float*)sr.p,
+                          (const float*)sc.p, (const float*)bias.p, (float*)f.p, f.ld, s);
+  });
 }
 
 // bind(addresses, get_device, get_stream): addresses of the library's entry

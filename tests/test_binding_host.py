@@ -55,3 +55,12 @@ def test_native_functions_decline():
     assert b.stream_terms([], 2, 4, None, False) is None
     with pytest.raises(TypeError):
         b.bind((1, 2), None, None)
+
+
+@pytest.mark.gpu
+def test_flag_without_truth_value_is_refused():
+    """A flag whose truth value raises is left to the Python code, which raises
+    the same error as before."""
+    x = torch.zeros(2, 64, device="cuda")
+    with pytest.raises(RuntimeError, match="ambiguous"):
+        m.mosaic_hadamard_rotate(x, torch.empty_like(x), inverse=torch.zeros(2))
