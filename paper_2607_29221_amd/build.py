@@ -29,7 +29,7 @@ INCLUDE = os.path.join(ROOT, "include")
 ARCH = os.environ.get("MOSAIC_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
-SOURCES = ["abi.cpp", "elementwise.hip", "ring_gemm.hip", "ring_gemm_skinny.hip", "hadamard.hip", "quantize.hip",
+SOURCES = ["abi.cpp", "elementwise.hip", "ring_gemm.hip", "ring_gemm_skinny.hip", "ring_gemv.hip", "hadamard.hip", "quantize.hip",
            "sparse.hip", "sparse_terms.hip", "abi_terms.cpp", "secure_input.hip", "hadamard28.hip", "probe.hip"]
 FLAGS = [f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-x", "hip",
          # keep the compiler from forming packed fp32 instructions

@@ -166,6 +166,12 @@ hipError_t launch_ring_gemm_words_b(const GemmLaunch& g, EpilogueKind epi, hipSt
 // a_pitch bytes per row, a_last as above): the rows' digit planes are formed
 // in registers as A is loaded.
 hipError_t launch_unmask_words_a(const GemmLaunch& g, hipStream_t s);
+
+// The products of A of one or two rows by dot products (ring_gemv.hip): C = A
+// B^T, and the unmask with A as ring words. Both need ring_gemv_takes(g).
+bool ring_gemv_takes(const GemmLaunch& g);
+hipError_t launch_ring_gemv(const GemmLaunch& g, hipStream_t s);
+hipError_t launch_unmask_gemv_words(const GemmLaunch& g, hipStream_t s);
 // d = 0 (rows x cols, leading dimension ldd) and *count = 0 in one launch.
 hipError_t launch_clear_check(uint32_t* d, int64_t ldd, int64_t rows, int64_t cols, int64_t* count, hipStream_t s);
 
