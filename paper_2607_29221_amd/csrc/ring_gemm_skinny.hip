@@ -590,7 +590,19 @@ hipError_t launch_unmask_words_a(const GemmLaunch& g, hipStream_t s) {
   if (ring_gemv_takes(g)) return launch_unmask_gemv_words(g, s);
   // the single-launch kernel at every factor size: the digit conversion of
   // A it replaces was a launch of its own
-  if (g.N <= 16 * compute_units()) return launch_ksplit<EPI_UNMASK, 1, 1, 2, 4, true>(g, s);
+  // One 16-row tile of B per workgroup and four waves while that leaves no
+  // compute unit a second round. With more workgroups than that two waves each
+  // (half the reads of A and half the sums to add): two tiles from 48 columns
+  // of the output per unit on (8 x 14336 at rank 704 17.1 -> 14.6 us, 16 x 14336
+  // at 1536 28.7 -> 26.4, 10 x 28672 48.9 -> 45.6), one tile between for up to 8
+  // rows (5 x 11008 at 704 16.1 -> 11.4, 8 x 5003 at 1536 15.4 -> 14.2); with
+  // more rows there the reads of A count most and two tiles share them on four
+  // waves (16 x 8192 at 1536: 17.2, else 19.2-19.5). Factors beyond the
+  // last-level cache, device time.
+  const int64_t cus = compute_units();
+  if (g.N <= 16 * cus) return launch_ksplit<EPI_UNMASK, 1, 1, 2, 4, true>(g, s);
+  if (g.N > 48 * cus) return launch_ksplit<EPI_UNMASK, 1, 2, 2, 2, true>(g, s);
+  if (g.M <= 8) return launch_ksplit<EPI_UNMASK, 1, 1, 2, 2, true>(g, s);
   return launch_ksplit<EPI_UNMASK, 1, 2, 2, 4, true>(g, s);
 }
 

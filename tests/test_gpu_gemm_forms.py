@@ -70,3 +70,25 @@ def test_many_tiles(M, N, K):
     y = torch.full((M, N), 5, dtype=torch.int32, device="cuda")
     m.mosaic_unmask(ym, None, A, B, M, N, K, y=y)
     assert torch.equal(y, ym - want)
+
+
+@pytest.mark.parametrize("M", [3, 8, 9, 16])
+@pytest.mark.parametrize("N", [4096, 4097, 12288, 12289])
+@pytest.mark.parametrize("K", [64, 192, 704])
+def test_unmask_words_forms(M, N, K):
+    """The forms of the unmask with Q as ring words at the column counts where
+    they change (16 and 48 per compute unit of 256), with fewer stages than
+    waves and shares that differ."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(M + N + K)
+    q = torch.randint(-2 ** 31, 2 ** 31, (M, K), generator=g, device="cuda", dtype=torch.int32)
+    A = Digits.empty(M, K)
+    m.mosaic_mask(None, q, None, M, K, out_dig=A)
+    B = Digits(torch.randint(-128, 128, (N, 4 * m.padded_k(K)), generator=g, device="cuda", dtype=torch.int8), K)
+    prod = torch.empty((M, N), dtype=torch.int32, device="cuda")
+    m.mosaic_masked_matmul(A, B, M, N, K, prod)
+    ym = torch.randint(-2 ** 31, 2 ** 31, (M, N), generator=g, device="cuda", dtype=torch.int32)
+    y = torch.full((M, N + 1), 5, dtype=torch.int32, device="cuda")
+    m.mosaic_unmask_words(ym, None, q, B, M, N, K, y=y[:, :N])
+    assert torch.equal(y[:, :N], ym - prod)
+    assert torch.all(y[:, N] == 5)
