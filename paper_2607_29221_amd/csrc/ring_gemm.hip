@@ -530,7 +530,10 @@ GemmPlan choose_plan(int64_t M, int64_t N, int64_t stages, int64_t cus, Epilogue
   const double half = (double)((t64 + cus - 1) / cus);   // tiles of 64 rows per unit, rounded up
   const double power = 0.55 * (double)t64 / (double)cus * S, reach = 0.38 * half * S;
   const double c64 = t64 <= cus ? 0.45 * S + 3.0 : (power > reach ? power : reach) + 8.0;
-  if (c64 < best) plan = GemmPlan{t64 <= cus ? FORM_64K : FORM_64, 0, 1};
+  // From eight whole rounds on, a partial last one matters less than the
+  // estimates' error, and FORM_64's operand traffic decides (28672 x 8192 x 1536,
+  // 56 rounds: 3050-3100 us, with FORM_128 2780)
+  if (c64 < best && full < 8) plan = GemmPlan{t64 <= cus ? FORM_64K : FORM_64, 0, 1};
   return plan;
 }
 
