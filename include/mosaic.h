@@ -315,7 +315,8 @@ mosaic_status mosaic_sparse_gather_cols(int64_t M, int64_t N, const int64_t* row
  * single calls one after the other. A term of the first is (rng, rcols, d,
  * ldd) of mosaic_sparse_stream_gather_rows; a term of the second adds to the
  * operands of mosaic_sparse_gather_cols the number of columns of its P (the
- * column indices are below it; ldd >= cols). nterms >= 1 for the second. */
+ * column indices are below it); the first cols words of each row of d are
+ * read, rows may overlap (ldd >= 0). nterms >= 1 for the second. */
 typedef struct mosaic_stream_term {
   mosaic_rng rng;
   int64_t rcols;

@@ -48,7 +48,8 @@ mosaic_status mosaic_sparse_gather_cols_terms(const mosaic_sparse_term* terms, i
     const mosaic_sparse_term& x = terms[l];
     if (x.row_ptr == nullptr || x.col_idx == nullptr || x.values == nullptr || x.d == nullptr)
       return fail(MOSAIC_ERR_INVALID_ARG, "NULL operand");
-    if (x.cols < 0 || x.ldd < x.cols) return fail(MOSAIC_ERR_INVALID_ARG, "ldd < cols");
+    // rows of d may share memory (ldd < cols), as in the single call
+    if (x.cols < 0 || x.ldd < 0) return fail(MOSAIC_ERR_INVALID_ARG, "negative cols or ldd");
     t[l] = SparseTerm{x.row_ptr, x.col_idx, x.values, x.d, x.ldd, x.cols};
   }
   const Dequant dq{s_rows, s_cols, bias, y_f32, ldf};

@@ -419,7 +419,7 @@ FUNCTION(cols_terms, 8) {
     NEED(attr_ptr(p, s_row_ptr, at::kLong, &rp) && attr_ptr(p, s_col_idx, at::kInt, &ci) &&
          attr_ptr(p, s_values, at::kInt, &va) && matrix(PyTuple_GET_ITEM(t, 1), M, cols, at::kInt, false, &d));
     terms[l] = mosaic_sparse_term{(const int64_t*)rp, (const int32_t*)ci, (const uint32_t*)va, cols,
-                                  (const uint32_t*)d.p, d.ld > cols ? d.ld : cols};
+                                  (const uint32_t*)d.p, d.ld};
   }
   Mat c, f, sr, sc, bias;
   NEED(matrix(a[2], M, N, at::kInt, false, &c) && matrix(a[4], M, N, at::kFloat, true, &f) &&

@@ -447,7 +447,7 @@ def mosaic_sparse_gather_cols_terms(terms: Sequence[Tuple[SparseRows, torch.Tens
             raise ValueError("the terms' matrices have different row counts")
         _need(d, M, p.cols, "d", _INT, optional=False)
         t.row_ptr, t.col_idx, t.values = p.row_ptr.data_ptr(), p.col_idx.data_ptr(), p.values.data_ptr()
-        t.cols, t.d, t.ldd = p.cols, d.data_ptr(), max(d.stride(0), p.cols)
+        t.cols, t.d, t.ldd = p.cols, d.data_ptr(), d.stride(0)
     _check(_lib.load().mosaic_sparse_gather_cols_terms(arr, len(terms), M, N, c.data_ptr(), c.stride(0),
                                                        1 if subtract else 0, _ptr(s_rows), _ptr(s_cols), _ptr(bias),
                                                        _ptr(y_f32), y_f32.stride(0) if y_f32 is not None else 0,

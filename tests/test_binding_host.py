@@ -57,6 +57,42 @@ def test_native_functions_decline():
         b.bind((1, 2), None, None)
 
 
+class _Recorder:
+    """Stands in for the native marshalling (declines) and for the library (records)."""
+
+    def __init__(self):
+        self.ldd = None
+
+    def cols_terms(self, *args):
+        return None
+
+    def mosaic_sparse_gather_cols_terms(self, terms, n, *args):
+        self.ldd = [terms[i].ldd for i in range(n)]
+        return 0
+
+
+class _DeviceLike:
+    """A host tensor that answers the shape checks as a device tensor would."""
+
+    def __init__(self, t):
+        self.t, self.is_cuda, self.dtype, self.shape = t, True, t.dtype, t.shape
+        self.dim, self.stride, self.data_ptr, self.numel = t.dim, t.stride, t.data_ptr, t.numel
+
+
+@pytest.mark.parametrize("stride", [0, 5, 64, 70])
+def test_gather_cols_terms_passes_the_row_stride(monkeypatch, stride):
+    """Rows of d that share memory (an expanded view) keep their stride: a longer
+    one would read past the view's storage."""
+    rec = _Recorder()
+    monkeypatch.setattr(m, "_b", rec)
+    monkeypatch.setattr(m._lib, "load", lambda: rec)
+    monkeypatch.setattr(m, "_stream", lambda: 0)
+    d = _DeviceLike(torch.zeros(1024, dtype=torch.int32).as_strided((8, 64), (stride, 1)))
+    p = m.SparseRows(_i32(4).long(), _i32(4), _i32(4), 3, 64)
+    m.mosaic_sparse_gather_cols_terms([(p, d)], 8, _DeviceLike(_i32(8, 3)))
+    assert rec.ldd == [stride]
+
+
 @pytest.mark.gpu
 def test_flag_without_truth_value_is_refused():
     """A flag whose truth value raises is left to the Python code, which raises

@@ -76,3 +76,20 @@ def test_gather_cols_terms(name, M, N):
     assert np.array_equal(to_np_u32(c), want)
     ref = (want.view(np.int32).astype(np.float32) * sr.cpu().numpy()[:, None]) * sc.cpu().numpy()[None, :]
     assert np.array_equal(y.cpu().numpy(), (ref + bias.cpu().numpy()[None, :]).astype(np.float32))
+
+
+@pytest.mark.parametrize("M", [1, 3, 8, 17])
+@pytest.mark.parametrize("stride", [0, 7])
+def test_gather_cols_terms_rows_that_overlap(M, stride):
+    """d as a view whose rows share memory, against the same matrix laid out in
+    full, staged in LDS and (wide rows) gathered from memory."""
+    rng = np.random.default_rng(M + stride)
+    N = 40
+    for cols in (64, 21000):
+        flat = to_dev_ring(rng.integers(0, 2 ** 32, (1, cols + stride * M), dtype=np.uint32))[0]
+        d = flat.as_strided((M, cols), (stride, 1))
+        p = m.mosaic_sparse_csr(m.rng(8, 0x61, 3, m.DIST_SPARSE, log2_inv_density=3), N, cols)
+        got, want = (torch.zeros((M, N), dtype=torch.int32, device="cuda") for _ in range(2))
+        m.mosaic_sparse_gather_cols_terms([(p, d)], M, got)
+        m.mosaic_sparse_gather_cols(p, d.contiguous(), M, want)
+        assert torch.equal(got, want)
