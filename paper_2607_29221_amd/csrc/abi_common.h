@@ -36,8 +36,6 @@ inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 
 
 inline int64_t padded_k(int64_t k) { return 64 * ((k + 63) / 64); }
 
-constexpr int64_t kMaxGridThreads = (int64_t(1) << 32) - 256;
-
 // Discrete Gaussian thresholds in extended precision (see mosaic.h).
 inline void dgauss_table(double sigma, int bound, uint64_t* out) {
   long double w[2 * kMaxDgaussBound + 1];

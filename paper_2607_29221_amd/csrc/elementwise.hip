@@ -3,8 +3,9 @@
 // rotation's sign vector, and unmasking without a product term.
 //
 // Contiguous rows take mask_quad_kernel, transposed plaintext and samples
-// mask_turn_kernel, anything else (plaintext with two strides, one of
-// plaintext and noise transposed) the general mask_kernel.
+// mask_turn_kernel, anything else (many short ragged rows, plaintext with two
+// strides, one of plaintext and noise transposed) the general mask_kernel; see
+// mask_route.
 #include "internal.h"
 
 namespace mosaic {
@@ -463,51 +464,45 @@ __global__ __launch_bounds__(256) void unmask_elementwise_kernel(GemmLaunch g) {
 }  // namespace
 
 hipError_t launch_mask(const MaskLaunch& a, hipStream_t s) {
-  // contiguous rows take mask_quad_kernel, its ragged form unless every row of
-  // every operand starts on a lane's own alignment (16 bytes of words, 4 of
-  // int8) and ends with a whole lane: the aligned form is the faster one there
-  // (no LDS, no partial lanes) and the ragged one cannot be needed
-  const bool x_row = a.x == nullptr || a.x_cs == 1;
-  const bool x_ok = a.x == nullptr ||
-                    (a.x_dtype == 0 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 3) == 0) ||
-                    (a.x_dtype >= 2 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 15) == 0);
-  const bool u_ok = a.u == nullptr || (a.ldu % 4 == 0 && ((uintptr_t)a.u & 15) == 0);
-  const bool o_ok = a.out == nullptr || (a.ldo % 4 == 0 && ((uintptr_t)a.out & 15) == 0);
-  const bool n_ok = !a.has_noise || !a.noise.transposed;
-  const int64_t lanes_per_row = (a.dig != nullptr) ? 64 * ((a.cols + 63) / 64) / 4 : 4 * ((a.cols + 15) / 16);
-  const int64_t blocks_per_row = (lanes_per_row + 255) / 256;
-  if (x_row && n_ok && a.rows * blocks_per_row <= 0x7FFFFFFF) {
-    if (a.rows == 0 || lanes_per_row == 0) return hipSuccess;
-    const uint32_t slices = (uint32_t)blocks_per_row;
+  if (a.rows <= 0 || a.cols <= 0) return hipSuccess;
+  MaskShape m{};
+  m.rows = a.rows;
+  m.cols = a.cols;
+  m.has_x = a.x != nullptr;
+  m.x_row = a.x_cs == 1;
+  m.x_turned = a.x_rs == 1;
+  m.has_noise = a.has_noise != 0;
+  m.noise_transposed = a.noise.transposed != 0;
+  m.digits = a.dig != nullptr;
+  m.aligned = a.cols % 4 == 0 &&
+              (a.x == nullptr || (a.x_dtype == 0 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 3) == 0) ||
+               (a.x_dtype >= 2 && a.x_rs % 4 == 0 && ((uintptr_t)a.x & 15) == 0)) &&
+              (a.u == nullptr || (a.ldu % 4 == 0 && ((uintptr_t)a.u & 15) == 0)) &&
+              (a.out == nullptr || (a.ldo % 4 == 0 && ((uintptr_t)a.out & 15) == 0));
+  const MaskRoute route = mask_route(m, compute_units());
+  const int xt = a.x == nullptr ? 0 : a.x_dtype == 0 ? 1 : a.x_dtype == 1 ? 3 : 2;
+  if (route == MASK_QUAD || route == MASK_QUAD_RAGGED) {
+    const int64_t lanes_per_row = m.digits ? 64 * ((a.cols + 63) / 64) / 4 : 4 * ((a.cols + 15) / 16);
     const int f = (a.u != nullptr ? MQ_U : 0) | (a.has_noise ? MQ_NOISE : 0) | (a.out != nullptr ? MQ_OUT : 0) |
                   (a.dig != nullptr ? MQ_DIG : 0);
-    const int xt = a.x == nullptr ? 0 : a.x_dtype == 0 ? 1 : a.x_dtype == 1 ? 3 : 2;
     MaskQuadLaunch go;
-    if (a.cols % 4 == 0 && x_ok && u_ok && o_ok)
+    if (route == MASK_QUAD)
       go = xt == 0 ? mask_quad_for<0, false>(f) : xt == 1 ? mask_quad_for<1, false>(f) : mask_quad_for<2, false>(f);
     else
       go = xt == 0 ? mask_quad_for<0, true>(f) : xt == 1 ? mask_quad_for<1, true>(f)
          : xt == 2 ? mask_quad_for<2, true>(f) : mask_quad_for<3, true>(f);
-    go(slices, a, lanes_per_row, s);
-    return hipGetLastError();
-  }
-  // transposed plaintext and transposed noise (or one of them alone): tiles
-  // turned through LDS; what remains for the general kernel is one of them
-  // transposed and the other not, and plaintext with two strides
-  const int64_t tiles_i = (a.rows + 63) / 64, tiles_j = (a.cols + 63) / 64;
-  if ((a.x == nullptr || a.x_rs == 1) && (!a.has_noise || a.noise.transposed) && tiles_i <= 0x7FFFFFFF / tiles_j) {
-    const uint32_t ti = (uint32_t)tiles_i, tj = (uint32_t)tiles_j;
-    if (a.x == nullptr) launch_mask_turn<0>(a, ti, tj, s);
-    else if (a.x_dtype == 0) launch_mask_turn<1>(a, ti, tj, s);
-    else if (a.x_dtype == 1) launch_mask_turn<3>(a, ti, tj, s);
+    go((uint32_t)mask_quad_slices(m), a, lanes_per_row, s);
+  } else if (route == MASK_TURN) {
+    const uint32_t ti = (uint32_t)((a.rows + 63) / 64), tj = (uint32_t)((a.cols + 63) / 64);
+    if (xt == 0) launch_mask_turn<0>(a, ti, tj, s);
+    else if (xt == 1) launch_mask_turn<1>(a, ti, tj, s);
+    else if (xt == 3) launch_mask_turn<3>(a, ti, tj, s);
     else launch_mask_turn<2>(a, ti, tj, s);
-    return hipGetLastError();
+  } else {
+    const int64_t groups = m.digits ? (64 * ((a.cols + 63) / 64)) / 16 : (a.cols + 15) / 16;
+    const int64_t blocks = (a.rows * groups + 255) / 256;
+    hipLaunchKernelGGL(mask_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, groups);
   }
-  const int64_t groups = (a.dig != nullptr) ? (64 * ((a.cols + 63) / 64)) / 16 : (a.cols + 15) / 16;
-  const int64_t threads = a.rows * groups;
-  if (threads == 0) return hipSuccess;
-  const int64_t blocks = (threads + 255) / 256;
-  hipLaunchKernelGGL(mask_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a, groups);
   return hipGetLastError();
 }
 

@@ -8,6 +8,7 @@
 #include <type_traits>
 
 #include "device_common.h"
+#include "dispatch.h"
 
 namespace mosaic {
 

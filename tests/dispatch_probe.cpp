@@ -1,0 +1,24 @@
+// The dispatch rules (csrc/dispatch.h) behind a C interface, for the tests.
+#include "../paper_2607_29221_amd/csrc/dispatch.h"
+
+using namespace mosaic;
+
+extern "C" {
+
+// flags: 1 plaintext, 2 its rows contiguous, 4 its columns, 8 aligned, 16
+// noise, 32 noise transposed, 64 digits
+int mask_route_of(int64_t rows, int64_t cols, int flags, int64_t cus) {
+  MaskShape a{};
+  a.rows = rows;
+  a.cols = cols;
+  a.has_x = (flags & 1) != 0;
+  a.x_row = (flags & 2) != 0;
+  a.x_turned = (flags & 4) != 0;
+  a.aligned = (flags & 8) != 0;
+  a.has_noise = (flags & 16) != 0;
+  a.noise_transposed = (flags & 32) != 0;
+  a.digits = (flags & 64) != 0;
+  return mask_route(a, cus);
+}
+
+}  // extern "C"

@@ -1,0 +1,32 @@
+"""The dispatch rules of csrc/dispatch.h, compiled by the host compiler."""
+import atexit
+import ctypes
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+i64 = ctypes.c_int64
+
+MASK_ROUTES = ("quad", "ragged", "turn", "general")
+
+
+@functools.lru_cache(maxsize=None)
+def _rules():
+    tmp = tempfile.mkdtemp(prefix="dispatch_rules")
+    atexit.register(shutil.rmtree, tmp, True)
+    so = os.path.join(tmp, "rules.so")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC",
+                    os.path.join(ROOT, "tests", "dispatch_probe.cpp"), "-o", so], check=True)
+    lib = ctypes.CDLL(so)
+    lib.mask_route_of.argtypes = [i64, i64, ctypes.c_int, i64]
+    return lib
+
+
+def mask_route(rows, cols, x=None, aligned=False, noise=None, digits=False, cus=256):
+    """x: None, "rows", "turned" or "strided"; noise: None, "rows" or "turned"."""
+    f = (x is not None) + 2 * (x == "rows") + 4 * (x == "turned") + 8 * aligned + 16 * (noise is not None) + \
+        32 * (noise == "turned") + 64 * digits
+    return MASK_ROUTES[_rules().mask_route_of(rows, cols, f, cus)]

@@ -104,3 +104,36 @@ def test_mask_transposed(rows, cols, kind, dtype):
     assert np.array_equal(got[:, 1: 1 + cols], want)
     assert np.all(got[:, 0] == 77) and np.all(got[:, 1 + cols:] == 77)
     assert np.array_equal(unpack_digits(dig), want) and pad_is_zero(dig)
+
+
+def test_mask_more_rows_than_a_launch_has_workgroups():
+    """2^24 rows and more: a workgroup per row would pass the launch limit of
+    2^32 threads, for ragged and for aligned rows."""
+    for cols in (3, 4):
+        rows = 2 ** 24 + 5
+        x = torch.arange(rows * cols, dtype=torch.int32, device="cuda").reshape(rows, cols)
+        out = torch.empty_like(x)
+        m.mosaic_mask(x, x, None, rows, cols, out=out)
+        assert torch.equal(out, 2 * x)
+
+
+@pytest.mark.parametrize("rows,cols", [(2049, 3), (6145, 17), (6144, 18)])
+@pytest.mark.parametrize("kind", ["uniform", "dgauss", "sparse"])
+def test_mask_many_short_rows(rows, cols, kind):
+    """Either side of the row count from which short ragged rows take the
+    general kernel."""
+    from oracle import sampling as smp
+    rng = np.random.default_rng(cols)
+    x = rng.integers(-2 ** 15, 2 ** 15, (rows, cols + 1)).astype(np.int16)
+    u = rng.integers(0, 2 ** 32, (rows, cols + 1), dtype=np.uint32)
+    e = smp.sample_matrix(kind, rows, cols, 91, 0x51, cols, sigma=0.5, bound=4, log2_inv_density=2)
+    want = ((x[:, 1:].astype(np.int64) + u[:, 1:] + e.astype(np.int64)) & 0xFFFFFFFF).astype(np.uint32)
+    out = torch.full((rows, cols + 2), 77, dtype=torch.int32, device="cuda")
+    dig = Digits.empty(rows, cols)
+    m.mosaic_mask(torch.from_numpy(x).cuda()[:, 1:], to_dev_ring(u)[:, 1:],
+                  m.rng(91, 0x51, cols, KINDS[kind], sigma=0.5, bound=4, log2_inv_density=2), rows, cols,
+                  out=out[:, 1: 1 + cols], out_dig=dig)
+    got = to_np_u32(out)
+    assert np.array_equal(got[:, 1: 1 + cols], want)
+    assert np.all(got[:, 0] == 77) and np.all(got[:, 1 + cols:] == 77)
+    assert np.array_equal(unpack_digits(dig), want) and pad_is_zero(dig)
