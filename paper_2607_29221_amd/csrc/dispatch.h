@@ -45,14 +45,22 @@ inline MaskRoute mask_route(const MaskShape& a, int64_t cus) {
     if (a.cols >= 192 || a.rows <= (a.cols >= 16 ? 24 : 8) * cus) return MASK_QUAD_RAGGED;
     return MASK_GENERAL;
   }
-  // Transposed plaintext and transposed noise (or one of them alone): tiles
-  // turned through LDS. What remains for the general kernel is one of them
-  // transposed and the other not, and plaintext with two strides.
-  const int64_t tiles_j = (a.cols + 63) / 64;
-  if ((!a.has_x || a.x_turned) && (!a.has_noise || a.noise_transposed) &&
-      (a.rows + 63) / 64 <= kMaxGridThreads / 256 / tiles_j)
-    return MASK_TURN;
-  return MASK_GENERAL;
+  // Transposed plaintext and transposed noise (or one of them alone): tiles of
+  // 64 x 64 turned through LDS, unless a side is so short that most of a tile
+  // is empty. That counts once there are more tiles than compute units; and
+  // where the rows are not a multiple of four, every lane's four noise elements
+  // lie across Philox blocks (two, of a sparse stream three). Device time,
+  // general / turned: uniform sample 1 x 2^20 8 / 71 us, 33 x 262144 24 / 29,
+  // 48 x 262144 34 / 23; sparse 65 x 512 7.3 / 10.3, 1 x 4096 6.9 / 9.8; int8 + u
+  // 2^20 x 3 13 / 43, 262144 x 16 13 / 15, 20 x 262144 20 / 14; dgauss 4 x 4096 10.0 /
+  // 5.3. What remains for the general kernel besides is one of plaintext and
+  // noise transposed and the other not, and plaintext with two strides.
+  const int64_t tiles_i = (a.rows + 63) / 64, tiles_j = (a.cols + 63) / 64;
+  if ((a.has_x && !a.x_turned) || (a.has_noise && !a.noise_transposed) || tiles_i > kMaxGridThreads / 256 / tiles_j)
+    return MASK_GENERAL;
+  const bool few = tiles_i * tiles_j <= cus;
+  const int64_t min_rows = !a.has_noise ? (few ? 2 : 12) : a.rows % 4 != 0 ? 128 : few ? 4 : 32;
+  return a.cols >= (few ? 6 : 17) && a.rows >= min_rows ? MASK_TURN : MASK_GENERAL;
 }
 
 }  // namespace mosaic

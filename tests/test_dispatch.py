@@ -39,3 +39,22 @@ def test_row_kernels_stay_within_a_launch(aligned, digits):
             if r in ("quad", "ragged"):
                 assert rows * per_row <= MAX_THREADS
             assert rows > fit or cols < 192 or r == ("quad" if aligned else "ragged")
+
+
+@pytest.mark.parametrize("rows,cols,x,noise", [
+    (1, 2 ** 20, None, "turned"), (2, 2 ** 20, "turned", None), (2 ** 20, 3, "turned", None), (65, 512, None, "turned"),
+    (8, 262144, "turned", "turned"), (1, 4096, None, "turned"), (33, 262144, None, "turned")])
+def test_turned_matrices_with_a_short_side(rows, cols, x, noise):
+    """64 x 64 tiles of which most is empty took up to 13 times as long."""
+    assert mask_route(rows, cols, x=x, noise=noise, digits=True) == "general"
+
+
+def test_turned_matrices():
+    assert mask_route(4096, 1536, x="turned", noise="turned") == "turn"
+    assert mask_route(1536, 4096, noise="turned", digits=True) == "turn"
+    assert mask_route(64, 64, x="turned") == "turn" and mask_route(2, 6, x="turned") == "turn"
+    assert mask_route(127, 2 ** 15, noise="turned") == "general" and mask_route(129, 2 ** 15, noise="turned") == "turn"
+    assert mask_route(12, 2 ** 20, x="turned") == "turn" and mask_route(11, 2 ** 20, x="turned") == "general"
+    assert mask_route(2 ** 20, 17, x="turned") == "turn" and mask_route(2 ** 20, 16, x="turned") == "general"
+    assert mask_route(2 ** 40, 2 ** 30, x="turned") == "general"     # more tiles than a launch has workgroups
+    assert mask_route(4096, 4096, x="turned", noise="rows") == "general"
