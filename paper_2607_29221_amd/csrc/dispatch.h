@@ -63,4 +63,34 @@ inline MaskRoute mask_route(const MaskShape& a, int64_t cus) {
   return a.cols >= (few ? 6 : 17) && a.rows >= min_rows ? MASK_TURN : MASK_GENERAL;
 }
 
+// ---------------------------------------------------------------------------
+// Products of one or two rows of A by dot products (ring_gemv.hip): which of
+// them are ahead of the matrix-core kernels, in M, N and the padded inner
+// dimension Kp. All kernels stream B, at 5-6 TB/s beyond a few megabytes, so
+// the dot products gain what stands around the stream, and lose where a wave's
+// own chain is long (long rows, too few of them to hide it) or its fixed cost
+// per two rows of B is (many short rows). A wave's sums fit 32 bits and its
+// LDS a compute unit's up to 6144 columns. Device time, B beyond the last-level
+// cache.
+
+// Store: the matrix-core kernel clears C first (a launch of its own) and adds
+// partial sums. One row, matrix cores / dot products: 4096 x 1536 9.5 / 7.3 us,
+// 8192 x 3072 22.6 / 19.3, 1024 x 4096 7.4 / 7.0, 3072 x 5120 15.5 / 14.3; but 200 x 4096
+// 5.8 / 6.2, 1024 x 5120 8.7 / 9.4, 2048 x 5120 11.8 / 12.1, 28672 x 128 7.0 / 8.5. Two rows
+// gain up to 2048 columns (8192 x 1536 13.9 / 12.3; 6656 x 4096 20.7 / 22.1) and
+// lose on many short rows sooner (16384 x 256 7.8 / 8.1, 28672 x 512 warm 13.4 / 13.8).
+inline bool gemv_takes_store(int64_t M, int64_t N, int64_t Kp) {
+  if (Kp <= 0 || N >= (int64_t(1) << 27) || (N > 8192 && Kp < 512)) return false;
+  if (M == 2) return Kp <= 2048;
+  return M == 1 && (Kp <= 3072 || (Kp <= 4096 && N >= 1024) || (Kp <= 6144 && N >= 3072));
+}
+
+// Unmask from ring words. One row: 64 x 6144 17.3 / 8.2 us, 4096 x 1536 9.6 / 7.8, 28672
+// x 6144 135 / 119; two rows: 4096 x 1536 9.6 / 8.6, 28672 x 2048 54 / 42. A single
+// chunk of 64 columns is behind with either: 16384 x 64 5.6 / 6.6 and 5.7 / 7.9.
+inline bool gemv_takes_unmask(int64_t M, int64_t N, int64_t Kp) {
+  if (Kp < 128 || N >= (int64_t(1) << 27)) return false;
+  return (M == 1 && Kp <= 6144) || (M == 2 && Kp <= 2048);
+}
+
 }  // namespace mosaic

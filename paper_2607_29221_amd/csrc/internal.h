@@ -169,8 +169,8 @@ hipError_t launch_ring_gemm_words_b(const GemmLaunch& g, EpilogueKind epi, hipSt
 hipError_t launch_unmask_words_a(const GemmLaunch& g, hipStream_t s);
 
 // The products of A of one or two rows by dot products (ring_gemv.hip): C = A
-// B^T, and the unmask with A as ring words. Both need ring_gemv_takes(g).
-bool ring_gemv_takes(const GemmLaunch& g);
+// B^T where gemv_takes_store says so, and the unmask with A as ring words where
+// gemv_takes_unmask does.
 hipError_t launch_ring_gemv(const GemmLaunch& g, hipStream_t s);
 hipError_t launch_unmask_gemv_words(const GemmLaunch& g, hipStream_t s);
 // d = 0 (rows x cols, leading dimension ldd) and *count = 0 in one launch.

@@ -10,7 +10,7 @@
 // padded only to 16, 32 or 64 rows.
 //
 // Two kernels (a store of one or two rows and the unmask that reads them as
-// words take ring_gemv.hip where ring_gemv_takes says so):
+// words take ring_gemv.hip where gemv_takes_store and gemv_takes_unmask say so):
 //
 // ring_gemm_skinny_kernel (store and accumulate epilogues). The unit of work
 // is one (column tile, stage) pair: 128 rows of B (output columns) against
@@ -587,7 +587,7 @@ hipError_t launch_unmask_words_a(const GemmLaunch& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
   if (g.M > 16) return hipErrorInvalidValue;
   if (g.Kp == 0) return launch_unmask_elementwise(g, s);
-  if (ring_gemv_takes(g)) return launch_unmask_gemv_words(g, s);
+  if (gemv_takes_unmask(g.M, g.N, g.Kp)) return launch_unmask_gemv_words(g, s);
   // the single-launch kernel at every factor size: the digit conversion of
   // A it replaces was a launch of its own
   // One 16-row tile of B per workgroup and four waves while that leaves no
@@ -667,7 +667,7 @@ hipError_t launch_ring_gemm_skinny(const GemmLaunch& g, EpilogueKind epi, hipStr
     if (mt == 2) return launch_ksplit<EPI_UNMASK, 2, 4, 1, 4>(g, s);
     return launch_ksplit<EPI_UNMASK, 4, 4, 1, 4>(g, s);
   }
-  if (epi == EPI_STORE && ring_gemv_takes(g)) return launch_ring_gemv(g, s);
+  if (epi == EPI_STORE && gemv_takes_store(g.M, g.N, g.Kp)) return launch_ring_gemv(g, s);
   // MT: 16-row tiles of A (33-64 rows padded to 64: faster than 48 rows on
   // one row of waves); WM: rows of 4 waves
   if (mt <= 1) return launch_shared_a<1, 1>(g, epi, s);

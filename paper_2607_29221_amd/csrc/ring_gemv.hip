@@ -189,21 +189,6 @@ hipError_t launch_rows(const GemmLaunch& g, hipStream_t s) {
 
 }  // namespace
 
-// One row of A, and two against short rows of B. Both kernels stream B, at
-// sizes up to the last-level cache at 5-6 TB/s, so one row gains what stands
-// around the stream: 4096 x 1536 (store) 6.2 -> 4.4 us, 8192 x 1536 11.4 -> 9.7,
-// 6656 x 4096 19.5 -> 19.3, 4096 x 6144 18.6 -> 17.2; unmask 4096 x 1536 6.7 ->
-// 4.7, 16384 x 1536 21.2 -> 16.8. With longer rows the stream is long, the chain
-// of a wave's steps too, and A leaves few waves room in LDS: 6656 x 8192 35.3 ->
-// 37.6, 64 x 8192 5.8 -> 7.4. (1024 x 4096, 5.3 -> 5.9, still saves a launch's
-// host time.) The dot products cost 2 us per row of A and 16 steps of a wave:
-// two rows gain up to 2048 columns (8192 x 1536 11.6 -> 11.0, 6656 x 2048 12.5 ->
-// 10.8) and lose beyond (6656 x 4096 20.7 -> 22.1), three lose at most sizes
-// (8192 x 1536 11.9 -> 14.6).
-bool ring_gemv_takes(const GemmLaunch& g) {
-  return g.Kp > 0 && ((g.M == 1 && g.Kp <= 6144) || (g.M == 2 && g.Kp <= 2048)) && g.N < (int64_t(1) << 27);
-}
-
 hipError_t launch_ring_gemv(const GemmLaunch& g, hipStream_t s) { return launch_rows<EPI_STORE, false>(g, s); }
 
 hipError_t launch_unmask_gemv_words(const GemmLaunch& g, hipStream_t s) {

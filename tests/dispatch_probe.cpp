@@ -21,4 +21,8 @@ int mask_route_of(int64_t rows, int64_t cols, int flags, int64_t cus) {
   return mask_route(a, cus);
 }
 
+int gemv_takes(int64_t M, int64_t N, int64_t Kp, int unmask) {
+  return unmask != 0 ? gemv_takes_unmask(M, N, Kp) : gemv_takes_store(M, N, Kp);
+}
+
 }  // extern "C"

@@ -22,6 +22,7 @@ def _rules():
                     os.path.join(ROOT, "tests", "dispatch_probe.cpp"), "-o", so], check=True)
     lib = ctypes.CDLL(so)
     lib.mask_route_of.argtypes = [i64, i64, ctypes.c_int, i64]
+    lib.gemv_takes.argtypes = [i64, i64, i64, ctypes.c_int]
     return lib
 
 
@@ -30,3 +31,8 @@ def mask_route(rows, cols, x=None, aligned=False, noise=None, digits=False, cus=
     f = (x is not None) + 2 * (x == "rows") + 4 * (x == "turned") + 8 * aligned + 16 * (noise is not None) + \
         32 * (noise == "turned") + 64 * digits
     return MASK_ROUTES[_rules().mask_route_of(rows, cols, f, cus)]
+
+
+def gemv(M, N, K, unmask):
+    """Whether a product of M rows of A takes the dot-product kernel."""
+    return bool(_rules().gemv_takes(M, N, 64 * -(-K // 64), unmask))

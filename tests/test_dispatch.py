@@ -2,7 +2,7 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import mask_route
+from tests.dispatch_util import gemv, mask_route
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -58,3 +58,18 @@ def test_turned_matrices():
     assert mask_route(2 ** 20, 17, x="turned") == "turn" and mask_route(2 ** 20, 16, x="turned") == "general"
     assert mask_route(2 ** 40, 2 ** 30, x="turned") == "general"     # more tiles than a launch has workgroups
     assert mask_route(4096, 4096, x="turned", noise="rows") == "general"
+
+
+def test_products_of_one_or_two_rows():
+    """Dot products only where they are ahead: not on few long rows of B, many
+    short ones, or a single chunk of columns."""
+    for M, N, K in ((1, 1024, 5120), (1, 64, 4096), (1, 200, 6144), (1, 28672, 128), (2, 16384, 256), (3, 4096, 1536),
+                    (1, 8192, 6208), (2, 4096, 2112)):
+        assert not gemv(M, N, K, unmask=False)
+    for M, N, K in ((1, 4096, 1536), (1, 1024, 4096), (1, 3072, 6144), (1, 64, 3072), (2, 8192, 2048), (1, 28672, 512),
+                    (1, 8192, 64)):
+        assert gemv(M, N, K, unmask=False)
+    for M, N, K in ((1, 28672, 64), (2, 4096, 64), (1, 64, 6208), (2, 64, 2112), (3, 64, 128), (1, 2 ** 27, 128)):
+        assert not gemv(M, N, K, unmask=True)
+    for M, N, K in ((1, 64, 65), (1, 28672, 6144), (2, 16384, 2048)):
+        assert gemv(M, N, K, unmask=True)

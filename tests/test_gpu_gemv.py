@@ -33,7 +33,7 @@ def _digits(x, col0=0):
 
 
 SIZES = [(1, N, K) for N in (1, 2, 7, 9, 257) for K in (1, 64, 100, 256, 260, 1024, 1088, 3000)]
-SIZES += [(1, 70, 6144), (1, 70, 6208), (2, 1, 64), (2, 9, 260), (2, 130, 1028), (2, 33, 2048), (2, 33, 2112)]
+SIZES += [(1, 1025, 4096), (1, 3073, 6144), (1, 70, 6144), (1, 70, 6208), (2, 1, 64), (2, 9, 260), (2, 130, 1028), (2, 33, 2048), (2, 33, 2112)]
 
 
 @pytest.mark.parametrize("M,N,K", SIZES)
