@@ -93,4 +93,25 @@ inline bool gemv_takes_unmask(int64_t M, int64_t N, int64_t Kp) {
   return (M == 1 && Kp <= 6144) || (M == 2 && Kp <= 2048);
 }
 
+// Unmask from ring words of 3 to 16 rows (ring_gemm_skinny.hip): 16-row tiles of
+// B and waves per workgroup. One tile and four waves while that leaves no
+// compute unit a second round. Beyond, two waves halve the reads of A and the
+// sums to add, which is most of the time with a short inner dimension, but a
+// long one is left with too few loads in flight. Beyond 48 columns of the
+// output per unit: two tiles, on two waves up to 3072 columns of the inner
+// dimension (four / two waves, factors beyond the last-level cache: 8 x 14336 at
+// 704 17.8 / 15.3 us, 16 x 14336 at 1536 28.7 / 26.3, 10 x 28672 at 2560 58 / 55;
+// at 4096 61 / 71, and at 64 5.9 / 6.5). From 16 to 48, for up to 8 rows: one tile on
+// two waves, beyond 32 per unit up to 6144 (8 x 11008 at 1536 24.9 / 20.5, at 4096
+// 57 / 48; 3 x 12288 at 8192 91 / 98), below it up to 1024 (8 x 5003 at 704 11.7 /
+// 10.8; at 2560 19.8 / 21.2). With more rows there the reads of A count most and two tiles share
+// them on four waves (16 x 8192 at 1536: 17.2, else 19.2-19.5).
+enum UnmaskWordsForm { UNMASK_1_TILE_4_WAVES, UNMASK_2_TILES_4_WAVES, UNMASK_1_TILE_2_WAVES, UNMASK_2_TILES_2_WAVES };
+
+inline UnmaskWordsForm unmask_words_form(int64_t M, int64_t N, int64_t Kp, int64_t cus) {
+  if (N <= 16 * cus) return UNMASK_1_TILE_4_WAVES;
+  if (N > 48 * cus) return Kp >= 128 && Kp <= 3072 ? UNMASK_2_TILES_2_WAVES : UNMASK_2_TILES_4_WAVES;
+  return M <= 8 && Kp <= (N > 32 * cus ? 6144 : 1024) ? UNMASK_1_TILE_2_WAVES : UNMASK_2_TILES_4_WAVES;
+}
+
 }  // namespace mosaic

@@ -590,20 +590,12 @@ hipError_t launch_unmask_words_a(const GemmLaunch& g, hipStream_t s) {
   if (gemv_takes_unmask(g.M, g.N, g.Kp)) return launch_unmask_gemv_words(g, s);
   // the single-launch kernel at every factor size: the digit conversion of
   // A it replaces was a launch of its own
-  // One 16-row tile of B per workgroup and four waves while that leaves no
-  // compute unit a second round. With more workgroups than that two waves each
-  // (half the reads of A and half the sums to add): two tiles from 48 columns
-  // of the output per unit on (8 x 14336 at rank 704 17.1 -> 14.6 us, 16 x 14336
-  // at 1536 28.7 -> 26.4, 10 x 28672 48.9 -> 45.6), one tile between for up to 8
-  // rows (5 x 11008 at 704 16.1 -> 11.4, 8 x 5003 at 1536 15.4 -> 14.2); with
-  // more rows there the reads of A count most and two tiles share them on four
-  // waves (16 x 8192 at 1536: 17.2, else 19.2-19.5). Factors beyond the
-  // last-level cache, device time.
-  const int64_t cus = compute_units();
-  if (g.N <= 16 * cus) return launch_ksplit<EPI_UNMASK, 1, 1, 2, 4, true>(g, s);
-  if (g.N > 48 * cus) return launch_ksplit<EPI_UNMASK, 1, 2, 2, 2, true>(g, s);
-  if (g.M <= 8) return launch_ksplit<EPI_UNMASK, 1, 1, 2, 2, true>(g, s);
-  return launch_ksplit<EPI_UNMASK, 1, 2, 2, 4, true>(g, s);
+  switch (unmask_words_form(g.M, g.N, g.Kp, compute_units())) {
+    case UNMASK_1_TILE_4_WAVES: return launch_ksplit<EPI_UNMASK, 1, 1, 2, 4, true>(g, s);
+    case UNMASK_2_TILES_2_WAVES: return launch_ksplit<EPI_UNMASK, 1, 2, 2, 2, true>(g, s);
+    case UNMASK_1_TILE_2_WAVES: return launch_ksplit<EPI_UNMASK, 1, 1, 2, 2, true>(g, s);
+    default: return launch_ksplit<EPI_UNMASK, 1, 2, 2, 4, true>(g, s);
+  }
 }
 
 hipError_t launch_clear_check(uint32_t* d, int64_t ldd, int64_t rows, int64_t cols, int64_t* count, hipStream_t s) {

@@ -25,4 +25,8 @@ int gemv_takes(int64_t M, int64_t N, int64_t Kp, int unmask) {
   return unmask != 0 ? gemv_takes_unmask(M, N, Kp) : gemv_takes_store(M, N, Kp);
 }
 
+int unmask_words_form_of(int64_t M, int64_t N, int64_t Kp, int64_t cus) {
+  return unmask_words_form(M, N, Kp, cus);
+}
+
 }  // extern "C"

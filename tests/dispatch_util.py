@@ -23,6 +23,7 @@ def _rules():
     lib = ctypes.CDLL(so)
     lib.mask_route_of.argtypes = [i64, i64, ctypes.c_int, i64]
     lib.gemv_takes.argtypes = [i64, i64, i64, ctypes.c_int]
+    lib.unmask_words_form_of.argtypes = [i64] * 4
     return lib
 
 
@@ -36,3 +37,8 @@ def mask_route(rows, cols, x=None, aligned=False, noise=None, digits=False, cus=
 def gemv(M, N, K, unmask):
     """Whether a product of M rows of A takes the dot-product kernel."""
     return bool(_rules().gemv_takes(M, N, 64 * -(-K // 64), unmask))
+
+
+def unmask_words(M, N, K, cus=256):
+    """(16-row tiles of B, waves) per workgroup."""
+    return ((1, 4), (2, 4), (1, 2), (2, 2))[_rules().unmask_words_form_of(M, N, 64 * -(-K // 64), cus)]

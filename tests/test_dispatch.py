@@ -2,7 +2,7 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import gemv, mask_route
+from tests.dispatch_util import gemv, mask_route, unmask_words
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -73,3 +73,13 @@ def test_products_of_one_or_two_rows():
         assert not gemv(M, N, K, unmask=True)
     for M, N, K in ((1, 64, 65), (1, 28672, 6144), (2, 16384, 2048)):
         assert gemv(M, N, K, unmask=True)
+
+
+def test_unmask_from_words():
+    """Two waves per workgroup only while the inner dimension is short, or the
+    workgroups are many for one tile each."""
+    for M, N, K, want in ((16, 4096, 4096, (1, 4)), (3, 4097, 1024, (1, 2)), (8, 5003, 1025, (2, 4)), (9, 4097, 64, (2, 4)),
+                          (8, 8192, 4096, (2, 4)), (8, 8193, 4096, (1, 2)), (8, 12288, 64, (1, 2)), (16, 12288, 704, (2, 4)),
+                          (3, 12289, 64, (2, 4)), (16, 12289, 65, (2, 2)), (16, 28672, 3072, (2, 2)),
+                          (3, 16384, 3073, (2, 4)), (8, 12288, 6145, (2, 4))):
+        assert unmask_words(M, N, K) == want, (M, N, K)

@@ -92,3 +92,9 @@ def test_unmask_words_forms(M, N, K):
     m.mosaic_unmask_words(ym, None, q, B, M, N, K, y=y[:, :N])
     assert torch.equal(y[:, :N], ym - prod)
     assert torch.all(y[:, N] == 5)
+
+
+@pytest.mark.parametrize("M,N,K", [(8, 8192, 1088), (8, 8193, 1088), (16, 12289, 3136), (1, 12289, 6208)])
+def test_unmask_words_long_inner(M, N, K):
+    """Either side of the inner dimensions where those forms change."""
+    test_unmask_words_forms(M, N, K)
