@@ -114,4 +114,39 @@ inline UnmaskWordsForm unmask_words_form(int64_t M, int64_t N, int64_t Kp, int64
   return M <= 8 && Kp <= (N > 32 * cus ? 6144 : 1024) ? UNMASK_1_TILE_2_WAVES : UNMASK_2_TILES_4_WAVES;
 }
 
+// ---------------------------------------------------------------------------
+// Gathers with sparse matrices (sparse_terms.hip, sparse.hip)
+
+constexpr int COLS_LDS = 80 * 1024;       // LDS for staged rows of d: two workgroups per compute unit
+// Rows of P from which a workgroup of gather_cols_terms_kernel takes 64 of them
+// and not 32, which halves the staging of d (8 rows of d, 2 x 14336 rows of P
+// with 80 entries: 11.9 against 13.0 us); with fewer rows 32 keep twice as many
+// workgroups (one row of d, 4096 rows of P: 4.3 against 5.1 us).
+constexpr int64_t COLS_MANY_ROWS = 8192;
+
+// Rows of d (M x cols, cols of the widest of nterms matrices) that a workgroup
+// of gather_cols_terms_kernel stages for an N-row P: 1, 2, 4 or 8; 0: the
+// matrices one after the other by gather_cols_kernel, which reads d from memory.
+//
+// More staged rows read the entries of P fewer times but take longer to stage
+// (cols = 1536: 3.6 us for a whole call with one row, 5.8 with eight), so below
+// COLS_MANY_ROWS only as many as let all workgroups run at once, two per compute
+// unit (8 x 4096 with 24 entries per row: 4.4 us with two, 5.8 with eight, 6.5 with
+// one, 4.8 from memory).
+//
+// From memory: where no row fits; a single narrow matrix, whose rows are short
+// (8 x 28672 at 256 columns: 7.5 / 9.0 us); and wide ones, whose staging is paid
+// by every workgroup, unless the outputs are many (from memory / staged, 4096
+// columns of 64 to 80 entries 1 x 8192 4.2 / 5.6, 16 x 8192 13.9 / 13.0, 8 x 14336 15 /
+// 8.3; 8192 columns of 32 to 128 16 x 8192 17 / 28, 64 x 28672 154 / 144 and 234 / 159).
+inline int gather_cols_rows(int nterms, int64_t M, int64_t N, int64_t cols, int64_t cus) {
+  const bool many = N > COLS_MANY_ROWS;
+  if (4 * cols > COLS_LDS || (nterms == 1 && cols <= 512)) return 0;
+  if (cols > 8192 || (cols > 4096 && !(many && N >= 768 * 1024 / M)) || (cols > 2048 && N < 128 * 1024 / M)) return 0;
+  int mb = 1;
+  while (mb < 8 && mb < M && 4 * cols * 2 * mb <= COLS_LDS && (many || (M + mb - 1) / mb * ((N + 31) / 32) > 2 * cus))
+    mb *= 2;
+  return mb;
+}
+
 }  // namespace mosaic

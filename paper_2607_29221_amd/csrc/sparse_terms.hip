@@ -27,7 +27,6 @@ namespace {
 
 constexpr int DRAW_MAX = 2048;   // columns of a SPARSE row drawn in one go
 constexpr int INFLIGHT = 10;     // loads (entries) per lane in flight
-constexpr int COLS_LDS = 80 * 1024;   // staged rows of d: two workgroups per compute unit
 
 struct DrawTerm {
   RngArgs r;
@@ -264,9 +263,7 @@ template <int MB>
 void launch_cols(const ColsTerms& a, int64_t M, int64_t N, uint32_t* c, int64_t ldc, int subtract, const Dequant& dq,
                  hipStream_t s) {
   const unsigned gx = (unsigned)((M + MB - 1) / MB);
-  // 64 rows of P per workgroup halve the staging of d; with few rows 32 keep
-  // twice as many workgroups
-  if (N > 8192)
+  if (N > COLS_MANY_ROWS)
     hipLaunchKernelGGL((gather_cols_terms_kernel<MB, 512>), dim3(gx, (unsigned)((N + 63) / 64)), dim3(512), 0, s, a,
                        M, N, c, ldc, subtract, dq);
   else
@@ -330,7 +327,7 @@ hipError_t launch_sparse_stream_gather_rows(const RngArgs& r, int64_t rows, int6
 
 hipError_t launch_sparse_gather_cols_terms(const SparseTerm* terms, int nterms, int64_t M, int64_t N, uint32_t* c,
                                            int64_t ldc, int subtract, const Dequant& dq, hipStream_t s) {
-  if (M == 0 || N == 0 || nterms == 0) return hipSuccess;
+  if (M == 0 || N == 0) return hipSuccess;
   ColsTerms a{};
   a.n = nterms;
   int64_t cols = 0;
@@ -338,10 +335,8 @@ hipError_t launch_sparse_gather_cols_terms(const SparseTerm* terms, int nterms, 
     a.t[l] = terms[l];
     cols = terms[l].cols > cols ? terms[l].cols : cols;
   }
-  // rows of d staged together: up to 8, as many as the LDS holds of a level
-  int mb = M > 4 ? 8 : M > 2 ? 4 : (int)M;
-  while (mb > 1 && 4 * cols * mb > COLS_LDS) mb /= 2;
-  if (4 * cols * mb > COLS_LDS) {                             // a row of d does not fit: gather it from memory
+  const int mb = gather_cols_rows(nterms, M, N, cols, compute_units());
+  if (mb == 0) {                                              // gather d from memory, one matrix at a time
     for (int l = 0; l < nterms; ++l) {
       const Dequant last = l + 1 == nterms ? dq : Dequant{};
       const hipError_t e = launch_sparse_gather_cols(M, N, terms[l].row_ptr, terms[l].col_idx, terms[l].values,
@@ -350,7 +345,7 @@ hipError_t launch_sparse_gather_cols_terms(const SparseTerm* terms, int nterms, 
     }
     return hipSuccess;
   }
-  switch (mb) {
+  switch (mb) {                                               // at most COLS_LDS of staged rows
     case 1: launch_cols<1>(a, M, N, c, ldc, subtract, dq, s); break;
     case 2: launch_cols<2>(a, M, N, c, ldc, subtract, dq, s); break;
     case 4: launch_cols<4>(a, M, N, c, ldc, subtract, dq, s); break;

@@ -29,4 +29,8 @@ int unmask_words_form_of(int64_t M, int64_t N, int64_t Kp, int64_t cus) {
   return unmask_words_form(M, N, Kp, cus);
 }
 
+int gather_cols_rows_of(int nterms, int64_t M, int64_t N, int64_t cols, int64_t cus) {
+  return gather_cols_rows(nterms, M, N, cols, cus);
+}
+
 }  // extern "C"

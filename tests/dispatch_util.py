@@ -24,6 +24,7 @@ def _rules():
     lib.mask_route_of.argtypes = [i64, i64, ctypes.c_int, i64]
     lib.gemv_takes.argtypes = [i64, i64, i64, ctypes.c_int]
     lib.unmask_words_form_of.argtypes = [i64] * 4
+    lib.gather_cols_rows_of.argtypes = [ctypes.c_int] + [i64] * 4
     return lib
 
 
@@ -42,3 +43,8 @@ def gemv(M, N, K, unmask):
 def unmask_words(M, N, K, cus=256):
     """(16-row tiles of B, waves) per workgroup."""
     return ((1, 4), (2, 4), (1, 2), (2, 2))[_rules().unmask_words_form_of(M, N, 64 * -(-K // 64), cus)]
+
+
+def gather_cols(nterms, M, N, cols, cus=256):
+    """Rows of d staged per workgroup, 0 if they are read from memory."""
+    return _rules().gather_cols_rows_of(nterms, M, N, cols, cus)

@@ -2,7 +2,7 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import gemv, mask_route, unmask_words
+from tests.dispatch_util import gather_cols, gemv, mask_route, unmask_words
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -83,3 +83,19 @@ def test_unmask_from_words():
                           (3, 12289, 64, (2, 4)), (16, 12289, 65, (2, 2)), (16, 28672, 3072, (2, 2)),
                           (3, 16384, 3073, (2, 4)), (8, 12288, 6145, (2, 4))):
         assert unmask_words(M, N, K) == want, (M, N, K)
+
+
+def test_column_gathers():
+    """Eight rows of d staged by a handful of workgroups, and wide or narrow
+    matrices staged whole, had taken up to twice the single gather's time."""
+    for M, N, want in ((16, 1024, 1), (17, 1024, 2), (1, 4096, 1), (5, 4096, 2), (8, 4096, 2), (16, 4096, 4), (8, 8192, 4),
+                       (16, 8192, 8), (17, 8192, 8), (2, 8193, 2), (3, 8193, 4), (8, 14336, 8), (200, 256, 4)):
+        assert gather_cols(1, M, N, 1536) == want and gather_cols(2, M, N, 1536) == want, (M, N)
+    for nterms, M, N, cols, want in ((1, 8, 28672, 512, 0), (2, 8, 28672, 512, 8), (1, 8, 28672, 513, 8), (1, 8, 8192, 4096, 0),
+                                     (1, 16, 8192, 4096, 4), (1, 64, 8192, 8192, 0), (1, 64, 14336, 8192, 2),
+                                     (1, 200, 28672, 8193, 0), (1, 200, 28672, 2 ** 20, 0)):
+        assert gather_cols(nterms, M, N, cols) == want, (M, N, cols)
+    for M in (1, 2, 3, 7, 8, 64, 1000):
+        for N in (1, 33, 8192, 8193, 10 ** 6):
+            for cols in (1, 513, 2560, 2561, 5121, 8192, 20480, 20481):
+                assert 4 * cols * gather_cols(2, M, N, cols) <= 80 * 1024
