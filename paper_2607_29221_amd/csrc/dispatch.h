@@ -149,4 +149,23 @@ inline int gather_cols_rows(int nterms, int64_t M, int64_t N, int64_t cols, int6
   return mb;
 }
 
+// Row gathers whose rows are drawn inside the call (rows x ncols outputs, n
+// matrices, `entries` in a row of all of them, `weight`: the first is a WEIGHT
+// stream): true for the matrices one after the other by gather_rows_kernel, one
+// word per lane, false for all at once by gather_stream_terms_kernel, four. A
+// single matrix with few outputs, or with few entries to share between the
+// waves, has nothing to gain from the second, whose fixed cost is 0.3-0.8 us
+// higher. Single / all at once: WEIGHT rows of 80 entries 1 x 8192 6.7 / 7.1 us, 8 x
+// 5000 8.9 / 9.0, 16 x 5000 13.9 / 10.6; of 256 entries 1 x 8192 18.1 / 17.4; SPARSE rows
+// of 24 8 x 8192 7.3 / 6.3, 200 x 8192 32.6 / 36.4; of 4 64 x 8192 7.2 / 10.2, of 16
+// 5.1 / 5.7 for 8 x 8192. Two matrices save a launch (24 entries each, 8 x 8192: 12.2 /
+// 8.9) unless the launch is long (200 x 18432: 106 / 121).
+inline bool gather_rows_single(int n, bool weight, int64_t entries, int64_t rows, int64_t ncols, int64_t cus) {
+  const int64_t blocks = rows * ((ncols + 255) / 256);
+  if (n > 1) return entries < 32 * n && blocks > 24 * cus;
+  if (entries < 20 || (!weight && blocks < cus)) return true;
+  if (entries < 32) return blocks < cus || blocks > 6 * cus;
+  return weight && entries <= 128 && 2 * rows * ((ncols + 63) / 64) <= 5 * cus;
+}
+
 }  // namespace mosaic

@@ -279,6 +279,7 @@ hipError_t launch_sparse_stream_gather_rows_terms(const StreamTerm* terms, int n
   DrawTerms a{};
   size_t words = 0;
   bool fits = true;
+  int64_t entries = 0;                                               // a row's, of all levels (expected)
   for (int l = 0; l < nterms; ++l) {
     const StreamTerm& t = terms[l];
     const bool weight = t.r.dist == 4;
@@ -290,16 +291,14 @@ hipError_t launch_sparse_stream_gather_rows_terms(const StreamTerm* terms, int n
     d.ldd = t.ldd;
     d.off = (int32_t)words;
     d.cap = weight ? t.r.row_weight : (int32_t)t.rcols;
+    entries += weight ? t.r.row_weight : t.rcols >> (32 - t.r.sparse_shift);
     // long WEIGHT rows are drawn step by step, long SPARSE rows in chunks
     fits = fits && (weight ? t.r.row_weight <= WEIGHT_PAR_T : t.rcols <= DRAW_MAX);
     words += 2 * (size_t)(fits ? d.cap : 0) + (weight ? (weighted_scratch_bytes(t.rcols, t.r.row_weight) + 3) / 4 : 0);
   }
   if (a.n == 0) return hipSuccess;
-  // one SPARSE row per compute unit or fewer: the single gather, with 4-byte
-  // loads on as many workgroups, is 1 us ahead (5.8 against 6.8 us for one row
-  // of 1536 against 8192 columns)
-  const bool small = a.n == 1 && a.t[0].r.dist != 4 && rows * ((ncols + 255) / 256) < compute_units();
-  if (!fits || small || 4 * words > 48 * 1024) {
+  if (!fits || 4 * words > 48 * 1024 ||
+      gather_rows_single(a.n, a.t[0].r.dist == 4, entries, rows, ncols, compute_units())) {
     for (int l = 0; l < nterms; ++l) {
       const hipError_t e = launch_gather_stream_single(terms[l].r, rows, terms[l].rcols, terms[l].d, terms[l].ldd,
                                                        ncols, c, ldc, subtract, s);

@@ -2,7 +2,7 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import gather_cols, gemv, mask_route, unmask_words
+from tests.dispatch_util import gather_cols, gather_rows_single, gemv, mask_route, unmask_words
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -99,3 +99,15 @@ def test_column_gathers():
         for N in (1, 33, 8192, 8193, 10 ** 6):
             for cols in (1, 513, 2560, 2561, 5121, 8192, 20480, 20481):
                 assert 4 * cols * gather_cols(2, M, N, cols) <= 80 * 1024
+
+
+def test_row_gathers():
+    """A single matrix of few outputs or few entries per row, and long launches
+    over sparse rows, had become slower with all matrices at once."""
+    for n, weight, entries, rows, ncols in ((1, 1, 80, 1, 8192), (1, 1, 80, 8, 5000), (1, 1, 16, 64, 8192), (1, 0, 4, 200, 32768),
+                                            (1, 0, 24, 200, 8192), (1, 0, 24, 7, 8192), (2, 0, 48, 200, 18432),
+                                            (1, 0, 256, 1, 8192)):
+        assert gather_rows_single(n, weight, entries, rows, ncols)
+    for n, weight, entries, rows, ncols in ((1, 1, 80, 16, 5000), (1, 1, 256, 1, 8192), (1, 0, 24, 8, 8192), (2, 0, 40, 8, 18432),
+                                            (2, 1, 160, 200, 32768), (2, 1, 160, 1, 512), (1, 0, 256, 64, 8192)):
+        assert not gather_rows_single(n, weight, entries, rows, ncols)
