@@ -4,6 +4,8 @@
 
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace mosaic {
 
 // A launch holds fewer than 2^32 threads.
@@ -112,6 +114,87 @@ inline UnmaskWordsForm unmask_words_form(int64_t M, int64_t N, int64_t Kp, int64
   if (N <= 16 * cus) return UNMASK_1_TILE_4_WAVES;
   if (N > 48 * cus) return Kp >= 128 && Kp <= 3072 ? UNMASK_2_TILES_2_WAVES : UNMASK_2_TILES_4_WAVES;
   return M <= 8 && Kp <= (N > 32 * cus ? 6144 : 1024) ? UNMASK_1_TILE_2_WAVES : UNMASK_2_TILES_4_WAVES;
+}
+
+// ---------------------------------------------------------------------------
+// Tiled ring product (ring_gemm.hip): its form and split.
+//
+// The forms and what a product is estimated to take in each, in microseconds
+// on a chip of `cus` compute units. All of it follows from two rates. A compute
+// unit by itself takes 0.58 us for a stage (32 columns of the inner dimension)
+// of a 128 x 128 tile; with every unit busy on uniform digits the chip is
+// power-limited to 0.96 us a stage. The estimates rank the forms and are no
+// predictions: over 3100 products of 65-4096 rows, 1000-28672 columns and 16-512
+// stages half of them are within 7% of the time measured from 96 stages on
+// (nine in ten within 22%, the low side where rows of odd length or pitch or
+// few rows against many columns cost memory time) and within 14% below.
+//
+// FORM_128, 128 x 128 tiles: whole rounds at 0.96 us a stage, the last round at
+// what its tiles leave of the power, 7 us a round for the prologue and the
+// epilogue.
+// FORM_128 with its last round split along K (not for the unmask epilogue,
+// which needs whole products): that round's tiles run as k pieces each, added
+// into C atomically, at 5 us per million words added, and C cleared first for
+// a store. Only a round that would leave at least half of the units idle: a
+// last round on three quarters of them runs at higher clocks, and splitting it
+// measured no faster.
+// FORM_64K, 64 x 128 tiles, two groups of waves splitting the stages: for
+// products of at most one tile per unit. A tile costs a unit 0.45 us a stage,
+// so a short product on few units takes two thirds of FORM_128's time (200 x
+// 4608 x 1536 unmask: 23 against 34 us; 200 x 6144 x 4096: 57 against 80 us
+// whole, 66 split in two).
+// FORM_64, 64 x 128 tiles, two workgroups to a unit: half the work per tile
+// and no common rounds, so products of one and a bit, or two and a bit, rounds
+// of FORM_128 waste less of the last (333 x 14336 x 1536 unmask: 76 against
+// 91 us; 1024 x 6144 x 1536: 80 against 92 us), but 1.5 times the operand
+// traffic. Two tiles on a unit take 0.43 us a stage each when the stages are
+// many (192 x 14336 x 8192, one and a third tiles per unit: 252 us against 240
+// with FORM_128, 448 x 6539 x 8192 220 / 213), and a few tiles left over after
+// whole turns of the units another 0.15 (640 x 6539 x 4096, 2.03 tiles per unit: 170
+// against 151 us; 448 x 14336 x 2560, 3.06: 158 / 149). From eight whole rounds of
+// FORM_128 on a partial last one matters less than the estimates' error and
+// the traffic decides (28672 x 8192 x 1536, 56 rounds: 3050-3100 us, with
+// FORM_128 2780).
+enum GemmForm { FORM_128, FORM_64K, FORM_64 };
+
+struct GemmPlan {
+  GemmForm form;
+  int64_t split_tiles;       // tiles of the last round that run as pieces
+  int split_k;               // pieces of each
+};
+
+inline GemmPlan choose_plan(int64_t M, int64_t N, int64_t stages, int64_t cus, bool store, bool unmask) {
+  const int64_t tn = (N + 127) / 128;
+  const int64_t t128 = ((M + 127) / 128) * tn, t64 = ((M + 63) / 64) * tn;
+  const double S = (double)stages, full = (double)(t128 / cus);
+  const int64_t tail = t128 % cus;
+  const double whole = full * (0.96 * S + 7.0) + 2.0;
+  const auto round = [&](double share) { return (share * 0.96 > 0.58 ? share * 0.96 : 0.58) * S + 7.0; };
+
+  GemmPlan plan{FORM_128, 0, 1};
+  double best = whole + (tail > 0 ? round((double)tail / (double)cus) : 0.0);
+  if (!unmask && tail > 0 && 2 * tail < cus) {
+    for (int k : {2, 3, 4, 6, 8}) {
+      if (stages / 2 < 2 * (int64_t)k) break;            // a piece keeps at least two stage pairs
+      const double rounds = (double)((tail * k + cus - 1) / cus);
+      const double words = (double)tail * k * 128.0 * (double)(M < 128 ? M : 128);
+      const double work = 0.58 * S / k * rounds;
+      const double read = (double)tail * (double)tn / (double)t128 * 128 * 128 * S / 5.2e6;   // B once
+      const double cost = whole + (work > read ? work : read) + 7.0 * rounds + 5e-6 * words + (store ? 4.0 : 0.0);
+      if (cost < best) {
+        best = cost;
+        plan = GemmPlan{FORM_128, tail, k};
+      }
+    }
+  }
+  if (t64 <= cus) return 0.45 * S + 3.0 < best ? GemmPlan{FORM_64K, 0, 1} : plan;
+  const int64_t turns = (t64 + cus - 1) / cus;           // tiles of 64 rows per unit, rounded up
+  const double power = 0.55 * (double)t64 / (double)cus * S;
+  const double reach = (turns == 2 && stages >= 100 ? 0.43 : 0.38) * (double)turns * S;
+  const bool left_over = turns > 2 && t64 % cus != 0 && 10 * (t64 % cus) <= cus;
+  const double c64 = (power > reach ? power : reach) + 8.0 + (left_over ? 0.15 * S : 0.0);
+  if (c64 < best && full < 8) plan = GemmPlan{FORM_64, 0, 1};
+  return plan;
 }
 
 // ---------------------------------------------------------------------------

@@ -467,76 +467,6 @@ __global__ __launch_bounds__(256) void clear_split_tiles_kernel(GemmLaunch g) {
   }
 }
 
-// The forms of the kernel and what a product is estimated to take in each,
-// in microseconds on a chip of `cus` compute units (fitted to 65-2048 rows
-// against 4608-14336 columns at 48, 128 and 256 stages; within 10% of nearly
-// all of those). All of it follows from two rates. A compute unit by itself
-// takes 0.58 us for a stage of a 128 x 128 tile; with every unit busy on
-// uniform digits the chip is power-limited to 0.96 us a stage.
-//
-// FORM_128, 128 x 128 tiles: whole rounds at 0.96 us a stage, the last round at
-// what its tiles leave of the power, 7 us a round for the prologue and the
-// epilogue.
-// FORM_128 with its last round split along K (launch_ring_gemm; not for the
-// unmask epilogue, which needs whole products): that round's tiles run as k
-// pieces each, added into C atomically, at 5 us per million words added, and
-// C cleared first for a store. Only a round that would leave at least half of
-// the units idle: a last round on three quarters of them runs at higher
-// clocks, and splitting it measured no faster.
-// FORM_64K, 64 x 128 tiles, two groups of waves splitting the stages: for
-// products of at most one tile per unit. A tile costs a unit 0.45 us a stage,
-// so a short product on few units takes two thirds of FORM_128's time (200 x
-// 4608 x 1536 unmask: 23 against 34 us; 200 x 6144 x 4096: 57 against 80 us
-// whole, 66 split in two).
-// FORM_64, 64 x 128 tiles, two workgroups to a unit: half the work per tile
-// and no common rounds, so products of one and a bit, or two and a bit, rounds
-// of FORM_128 waste less of the last (333 x 14336 x 1536 unmask: 79 against
-// 90 us; 1024 x 6144 x 4096: 197 against 220 us), but 1.5 times the operand
-// traffic, which costs 2-6% where the rounds are full or many (2048 x 6144 x
-// 4096: 382 against 368 us).
-enum GemmForm { FORM_128, FORM_64K, FORM_64 };
-
-struct GemmPlan {
-  GemmForm form;
-  int64_t split_tiles;
-  int split_k;
-};
-
-GemmPlan choose_plan(int64_t M, int64_t N, int64_t stages, int64_t cus, EpilogueKind epi) {
-  const int64_t tn = (N + BN - 1) / BN;
-  const int64_t t128 = ((M + 127) / 128) * tn, t64 = ((M + 63) / 64) * tn;
-  const double S = (double)stages, full = (double)(t128 / cus);
-  const int64_t tail = t128 % cus;
-  const double whole = full * (0.96 * S + 7.0) + 2.0;
-  const auto round = [&](double share) { return (share * 0.96 > 0.58 ? share * 0.96 : 0.58) * S + 7.0; };
-
-  GemmPlan plan{FORM_128, 0, 1};
-  double best = whole + (tail > 0 ? round((double)tail / (double)cus) : 0.0);
-  if (epi != EPI_UNMASK && tail > 0 && 2 * tail < cus) {
-    for (int k : {2, 3, 4, 6, 8}) {
-      if (stages / 2 < 2 * (int64_t)k) break;            // a piece keeps at least two stage pairs
-      const double rounds = (double)((tail * k + cus - 1) / cus);
-      const double words = (double)tail * k * 128.0 * (double)(M < 128 ? M : 128);
-      const double work = 0.58 * S / k * rounds;
-      const double read = (double)tail * (double)tn / (double)t128 * BN * ROWB * S / 5.2e6;   // B once
-      const double cost = whole + (work > read ? work : read) + 7.0 * rounds + 5e-6 * words +
-                          (epi == EPI_STORE ? 4.0 : 0.0);
-      if (cost < best) {
-        best = cost;
-        plan = GemmPlan{FORM_128, tail, k};
-      }
-    }
-  }
-  const double half = (double)((t64 + cus - 1) / cus);   // tiles of 64 rows per unit, rounded up
-  const double power = 0.55 * (double)t64 / (double)cus * S, reach = 0.38 * half * S;
-  const double c64 = t64 <= cus ? 0.45 * S + 3.0 : (power > reach ? power : reach) + 8.0;
-  // From eight whole rounds on, a partial last one matters less than the
-  // estimates' error, and FORM_64's operand traffic decides (28672 x 8192 x 1536,
-  // 56 rounds: 3050-3100 us, with FORM_128 2780)
-  if (c64 < best && full < 8) plan = GemmPlan{t64 <= cus ? FORM_64K : FORM_64, 0, 1};
-  return plan;
-}
-
 template <class F, int EPI, bool SPLIT>
 void launch_form_epi(const GemmLaunch& g, dim3 grid, bool aligned, hipStream_t s) {
   if (aligned) hipLaunchKernelGGL((ring_gemm_kernel<F, EPI, true, SPLIT>), grid, dim3(F::NT), 0, s, g);
@@ -571,7 +501,7 @@ hipError_t launch_form(const GemmLaunch& g, EpilogueKind epi, hipStream_t s) {
 hipError_t launch_ring_gemm(const GemmLaunch& g, EpilogueKind epi, hipStream_t s) {
   if (g.M <= SKINNY_MAX_M) return launch_ring_gemm_skinny(g, epi, s);
   if (g.N <= 0) return hipSuccess;
-  GemmPlan p = choose_plan(g.M, g.N, g.Kp / BK, compute_units(), epi);
+  const GemmPlan p = choose_plan(g.M, g.N, g.Kp / BK, compute_units(), epi == EPI_STORE, epi == EPI_UNMASK);
   GemmLaunch gs = g;
   gs.split_tiles = p.split_tiles;
   gs.split_k = p.split_k;

@@ -37,4 +37,12 @@ int gather_rows_single_of(int n, int weight, int64_t entries, int64_t rows, int6
   return gather_rows_single(n, weight != 0, entries, rows, ncols, cus);
 }
 
+// epilogue: 0 store, 1 accumulate, 2 unmask
+void gemm_plan_of(int64_t M, int64_t N, int64_t Kp, int epilogue, int64_t cus, int64_t out[3]) {
+  const GemmPlan p = choose_plan(M, N, Kp / 32, cus, epilogue == 0, epilogue == 2);
+  out[0] = p.form;
+  out[1] = p.split_tiles;
+  out[2] = p.split_k;
+}
+
 }  // extern "C"

@@ -26,6 +26,7 @@ def _rules():
     lib.unmask_words_form_of.argtypes = [i64] * 4
     lib.gather_cols_rows_of.argtypes = [ctypes.c_int] + [i64] * 4
     lib.gather_rows_single_of.argtypes = [ctypes.c_int, ctypes.c_int] + [i64] * 4
+    lib.gemm_plan_of.argtypes = [i64, i64, i64, ctypes.c_int, i64, ctypes.POINTER(i64)]
     return lib
 
 
@@ -54,3 +55,11 @@ def gather_cols(nterms, M, N, cols, cus=256):
 def gather_rows_single(n, weight, entries, rows, ncols, cus=256):
     """Whether a row gather over n matrices runs them one after the other."""
     return bool(_rules().gather_rows_single_of(n, weight, entries, rows, ncols, cus))
+
+
+def gemm_plan(M, N, K, epilogue, cus=256):
+    """(form, tiles split, pieces of each) of a tiled product of M > 64 rows;
+    epilogue: "store", "accum" or "unmask"."""
+    out = (i64 * 3)()
+    _rules().gemm_plan_of(M, N, 64 * -(-K // 64), ("store", "accum", "unmask").index(epilogue), cus, out)
+    return ("128", "64k", "64")[out[0]], out[1], out[2]

@@ -2,7 +2,7 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import gather_cols, gather_rows_single, gemv, mask_route, unmask_words
+from tests.dispatch_util import gather_cols, gather_rows_single, gemm_plan, gemv, mask_route, unmask_words
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -111,3 +111,27 @@ def test_row_gathers():
     for n, weight, entries, rows, ncols in ((1, 1, 80, 16, 5000), (1, 1, 256, 1, 8192), (1, 0, 24, 8, 8192), (2, 0, 40, 8, 18432),
                                             (2, 1, 160, 200, 32768), (2, 1, 160, 1, 512), (1, 0, 256, 64, 8192)):
         assert not gather_rows_single(n, weight, entries, rows, ncols)
+
+
+def test_tiled_products_where_64_row_tiles_were_behind():
+    """A few tiles left over after whole turns of the units, and one and a bit
+    turns of many stages: 3-13% slower than with 128-row tiles."""
+    for M, N, K, epi in ((640, 6539, 4096, "store"), (640, 6539, 2560, "store"), (448, 14336, 2560, "store"),
+                         (333, 11008, 2560, "store"), (384, 11008, 2560, "store"), (448, 9728, 8192, "store"),
+                         (192, 14336, 8192, "store"), (160, 14336, 4096, "unmask"), (448, 6539, 8192, "store")):
+        assert gemm_plan(M, N, K, epi)[0] == "128", (M, N, K, epi)
+
+
+def test_tiled_products():
+    for M, N, K, epi, want in ((200, 4608, 1536, "unmask", ("64k", 0, 1)), (200, 6144, 4096, "store", ("64k", 0, 1)),
+                               (333, 14336, 1536, "unmask", ("64", 0, 1)), (1024, 6144, 1536, "store", ("64", 0, 1)),
+                               (28672, 8192, 1536, "store", ("128", 0, 1)), (2048, 28672, 8192, "store", ("128", 0, 1)),
+                               (128, 4608, 0, "store", ("64k", 0, 1))):
+        assert gemm_plan(M, N, K, epi) == want, (M, N, K, epi)
+    for M in (65, 200, 333, 2048):
+        for N in (1, 5003, 28672):
+            for K in (64, 704, 8192):
+                assert gemm_plan(M, N, K, "unmask")[1:] == (0, 1)      # needs whole products
+                for epi in ("store", "accum"):
+                    form, tiles, k = gemm_plan(M, N, K, epi)
+                    assert k == 1 or (form == "128" and 0 < 2 * tiles < 256 and K >= 128 * k)
