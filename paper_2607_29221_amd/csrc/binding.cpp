@@ -34,6 +34,7 @@ struct Abi {
 
 PyObject *s_buf, *s_col0, *s_row_ptr, *s_col_idx, *s_values, *s_rows, *s_cols;   // interned attribute names
 PyObject *get_device, *get_stream;                                               // torch._C functions
+PyObject* rng_type;                                                              // the ctypes struct of mosaic_rng
 
 struct Mat {
   void* p = nullptr;
@@ -108,6 +109,7 @@ class Rng {
  public:
   bool get(PyObject* o, bool optional) {
     if (o == Py_None) return optional;
+    if (!PyObject_TypeCheck(o, (PyTypeObject*)rng_type)) return false;
     if (PyObject_GetBuffer(o, &b_, PyBUF_SIMPLE) != 0) {
       PyErr_Clear();
       return false;
@@ -431,12 +433,13 @@ FUNCTION(cols_terms, 8) {
   });
 }
 
-// bind(addresses, get_device, get_stream): addresses of the library's entry
-// points in the order of Abi; torch._C's current device and raw stream.
+// bind(addresses, get_device, get_stream, rng_type): addresses of the library's
+// entry points in the order of Abi; torch._C's current device and raw stream;
+// the type that generators are of.
 PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
   constexpr Py_ssize_t count = sizeof(Abi) / sizeof(void*);
-  if (n != 3 || !PyTuple_CheckExact(a[0]) || PyTuple_GET_SIZE(a[0]) != count) {
-    PyErr_Format(PyExc_TypeError, "bind takes a tuple of %zd addresses and two functions", count);
+  if (n != 4 || !PyTuple_CheckExact(a[0]) || PyTuple_GET_SIZE(a[0]) != count || !PyType_Check(a[3])) {
+    PyErr_Format(PyExc_TypeError, "bind takes a tuple of %zd addresses, two functions and a type", count);
     return nullptr;
   }
   void* p[count];
@@ -448,12 +451,13 @@ PyObject* bind(PyObject*, PyObject* const* a, Py_ssize_t n) {
     }
   }
   memcpy(&abi, p, sizeof(p));
-  Py_INCREF(a[1]);
-  Py_INCREF(a[2]);
-  Py_XDECREF(get_device);
-  Py_XDECREF(get_stream);
-  get_device = a[1];
-  get_stream = a[2];
+  PyObject** const kept[] = {&get_device, &get_stream, &rng_type};
+  for (int i = 0; i < 3; ++i) {
+    PyObject* const old = *kept[i];
+    Py_INCREF(a[1 + i]);
+    *kept[i] = a[1 + i];
+    Py_XDECREF(old);
+  }
   Py_RETURN_NONE;
 }
 

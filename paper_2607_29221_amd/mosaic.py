@@ -54,7 +54,7 @@ def _native():
         lib = _lib.load()
         from . import _binding
         _binding.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND),
-                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+                      torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _lib.MosaicRng)
         _b = _binding
     return _b
 

@@ -54,7 +54,31 @@ def test_native_functions_decline():
     assert b.masked_matmul(object(), 5, 2, 3, 64, "c") is None
     assert b.stream_terms([], 2, 4, None, False) is None
     with pytest.raises(TypeError):
-        b.bind((1, 2), None, None)
+        b.bind((1, 2), None, None, m._lib.MosaicRng)
+
+
+def test_only_generators_are_taken_for_generators(monkeypatch):
+    """Any other object of the struct's size raises, as ctypes has it."""
+    import ctypes
+
+    import numpy as np
+    b = m._native()
+    args = [tuple(ctypes.cast(getattr(m._lib.load(), n), ctypes.c_void_p).value for n in m._BOUND),
+            lambda: 0, lambda device: 0, m._lib.MosaicRng]
+    monkeypatch.setattr(m, "_stream", lambda: 0)
+    b.bind(*args)                       # a current stream without a GPU; the library refuses calls without an output
+    try:
+        r = m.rng(1, 2, 3, m.DIST_UNIFORM)
+        size = ctypes.sizeof(r)
+        assert isinstance(b.sample(r, 4, 8, None, None), int)
+        for o in (bytes(size), bytearray(size), np.zeros(size, np.uint8), (ctypes.c_char * size)()):
+            assert b.sample(o, 4, 8, None, None) is None
+            assert b.mask(None, None, o, 4, 8, None, None, False) is None
+            assert b.stream_terms([(o, 8, None)], 2, 4, None, False) is None
+            with pytest.raises((TypeError, ctypes.ArgumentError)):
+                m.mosaic_sample(o, 4, 8)
+    finally:
+        b.bind(args[0], torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, m._lib.MosaicRng)
 
 
 class _Recorder:
