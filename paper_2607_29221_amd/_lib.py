@@ -105,6 +105,21 @@ def stale_reason() -> Optional[str]:
     return None
 
 
+def binding_stale_reason() -> Optional[str]:
+    """Why the in-tree _binding.so cannot be loaded, or None: it is missing, or
+    was compiled from other sources or against another torch or Python, whose
+    tensors it would read by a layout that is not theirs."""
+    from . import build as _build
+    for path in (_build.BINDING, _build.BINDING_STAMP):
+        if not os.path.exists(path):
+            return f"{path} is missing"
+    with open(_build.BINDING_STAMP) as f:
+        stamp = f.read().strip()
+    if stamp != _build.binding_digest():
+        return "its sources, flags, torch or Python changed after the last build"
+    return None
+
+
 def load() -> ctypes.CDLL:
     global _lib
     if _lib is None:

@@ -52,6 +52,9 @@ def _native():
     global _b
     if _b is None:
         lib = _lib.load()
+        why = _lib.binding_stale_reason()
+        if why is not None:
+            raise RuntimeError(f"_binding.so is not usable ({why}): run `python -m paper_2607_29221_amd.build`")
         from . import _binding
         _binding.bind(tuple(ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _BOUND),
                       torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, _lib.MosaicRng)

@@ -81,6 +81,30 @@ def test_only_generators_are_taken_for_generators(monkeypatch):
         b.bind(args[0], torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream, m._lib.MosaicRng)
 
 
+def test_binding_of_another_torch_or_python_is_refused(monkeypatch, tmp_path):
+    """_binding.so reads tensors by the layout of the torch it was compiled
+    against: it is not loaded into another one, nor without its stamp."""
+    import shutil
+    from paper_2607_29221_amd import build
+    assert m._lib.binding_stale_reason() is None
+    monkeypatch.setattr(m, "_b", None)
+    with monkeypatch.context() as c:
+        c.setattr(torch, "__version__", "0.0.1")
+        with pytest.raises(RuntimeError, match="run `python -m"):
+            m._native()
+    for name in ("BINDING", "BINDING_STAMP"):
+        with monkeypatch.context() as c:
+            c.setattr(build, name, str(tmp_path / name))
+            with pytest.raises(RuntimeError, match="is missing"):
+                m._native()
+    with monkeypatch.context() as c:
+        shutil.copytree(build.CSRC, tmp_path / "csrc")
+        (tmp_path / "csrc" / "binding.cpp").write_text("// edited")
+        c.setattr(build, "CSRC", str(tmp_path / "csrc"))
+        assert "changed" in m._lib.binding_stale_reason()
+    assert m._native() is not None
+
+
 class _Recorder:
     """Stands in for the native marshalling (declines) and for the library (records)."""
 
