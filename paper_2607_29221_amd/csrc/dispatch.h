@@ -8,8 +8,21 @@
 
 namespace mosaic {
 
-// A launch holds fewer than 2^32 threads.
+// A launch holds fewer than 2^32 threads (along its first dimension): the
+// runtime takes a larger one without an error and runs the remainder modulo
+// 2^32 only.
 constexpr int64_t kMaxGridThreads = (int64_t(1) << 32) - 256;
+
+// Cuts rows x units (the units of a row side by side, such as the blocks of a
+// rotation) into launches of at most `most` units: whole rows, or parts of one
+// row where a row has more. f(row0, rows, unit0, units) returns true to go on.
+template <class F>
+inline void for_each_launch(int64_t rows, int64_t units, int64_t most, F f) {
+  const int64_t per_u = units < most ? units : most, per_r = units < most ? most / units : 1;
+  for (int64_t r = 0; r < rows; r += per_r)
+    for (int64_t u = 0; u < units; u += per_u)
+      if (!f(r, rows - r < per_r ? rows - r : per_r, u, units - u < per_u ? units - u : per_u)) return;
+}
 
 // ---------------------------------------------------------------------------
 // Mask pass (elementwise.hip)

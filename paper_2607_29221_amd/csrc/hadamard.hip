@@ -79,11 +79,10 @@ __global__ __launch_bounds__(256) void fwht_short_kernel(const float* __restrict
 }
 
 template <int LOGB>
-hipError_t launch_fwht_short(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
-                             const int8_t* signs, int inverse, hipStream_t s) {
+void launch_fwht_short(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
+                       const int8_t* signs, int inverse, hipStream_t s) {
   const int64_t n4 = n / 4, total = rows * n4;
-  if (total == 0) return hipSuccess;
-  const dim3 grid((unsigned)((total + 255) / 256));   // below 2^31: at most 2^31 blocks of b >= 16
+  const dim3 grid((unsigned)((total + 255) / 256));
   const float scale = (float)(1.0 / sqrt((double)(1 << LOGB)));
   if (signs == nullptr)
     hipLaunchKernelGGL((fwht_short_kernel<LOGB, 0>), grid, dim3(256), 0, s, x, ldx, y, ldy, n4, total, signs, scale);
@@ -91,17 +90,15 @@ hipError_t launch_fwht_short(const float* x, int64_t ldx, float* y, int64_t ldy,
     hipLaunchKernelGGL((fwht_short_kernel<LOGB, 1>), grid, dim3(256), 0, s, x, ldx, y, ldy, n4, total, signs, scale);
   else
     hipLaunchKernelGGL((fwht_short_kernel<LOGB, 2>), grid, dim3(256), 0, s, x, ldx, y, ldy, n4, total, signs, scale);
-  return hipGetLastError();
 }
 
 template <int LOGB>
-hipError_t launch_fwht(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
-                       const int8_t* signs, int inverse, hipStream_t s) {
+void launch_fwht(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
+                 const int8_t* signs, int inverse, hipStream_t s) {
   constexpr int B = FwhtShape<LOGB, fwht_tmax(LOGB)>::B;
   constexpr int T = FwhtShape<LOGB, fwht_tmax(LOGB)>::T;
   const int64_t bpr = n / B;
   const int64_t grid = rows * bpr;
-  if (grid == 0) return hipSuccess;
   const float scale = (float)(1.0 / sqrt((double)B));
   if (signs == nullptr)
     hipLaunchKernelGGL((fwht_kernel<LOGB, 0>), dim3((unsigned)grid), dim3(T), 0, s, x, ldx, y, ldy, bpr, signs,
@@ -112,6 +109,21 @@ hipError_t launch_fwht(const float* x, int64_t ldx, float* y, int64_t ldy, int64
   else
     hipLaunchKernelGGL((fwht_kernel<LOGB, 2>), dim3((unsigned)grid), dim3(T), 0, s, x, ldx, y, ldy, bpr, signs,
                        scale);
+}
+
+// The rotation in as many launches as its threads need (one up to 2^34 elements).
+template <int LOGB>
+hipError_t launch_parts(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
+                        const int8_t* signs, int inverse, hipStream_t s) {
+  constexpr int64_t B = 1 << LOGB, T = FwhtShape<LOGB, fwht_tmax(LOGB)>::T;   // threads of a block (B / 4 if short)
+  for_each_launch(rows, n / B, kMaxGridThreads / T, [&](int64_t r0, int64_t nr, int64_t b0, int64_t nb) {
+    const float* xp = x + r0 * ldx + b0 * B;
+    float* yp = y + r0 * ldy + b0 * B;
+    const int8_t* sp = signs != nullptr ? signs + b0 * B : nullptr;
+    if constexpr (LOGB <= 7) launch_fwht_short<LOGB>(xp, ldx, yp, ldy, nr, nb * B, sp, inverse, s);
+    else launch_fwht<LOGB>(xp, ldx, yp, ldy, nr, nb * B, sp, inverse, s);
+    return hipPeekAtLastError() == hipSuccess;
+  });
   return hipGetLastError();
 }
 
@@ -120,18 +132,18 @@ hipError_t launch_fwht(const float* x, int64_t ldx, float* y, int64_t ldy, int64
 hipError_t launch_hadamard(const float* x, int64_t ldx, float* y, int64_t ldy, int64_t rows, int64_t n,
                            int log2_block, const int8_t* signs, int inverse, hipStream_t s) {
   switch (log2_block) {
-    case 4: return launch_fwht_short<4>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 5: return launch_fwht_short<5>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 6: return launch_fwht_short<6>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 7: return launch_fwht_short<7>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 8: return launch_fwht<8>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 9: return launch_fwht<9>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 10: return launch_fwht<10>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 11: return launch_fwht<11>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 12: return launch_fwht<12>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 13: return launch_fwht<13>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 14: return launch_fwht<14>(x, ldx, y, ldy, rows, n, signs, inverse, s);
-    case 15: return launch_fwht<15>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 4: return launch_parts<4>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 5: return launch_parts<5>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 6: return launch_parts<6>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 7: return launch_parts<7>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 8: return launch_parts<8>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 9: return launch_parts<9>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 10: return launch_parts<10>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 11: return launch_parts<11>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 12: return launch_parts<12>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 13: return launch_parts<13>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 14: return launch_parts<14>(x, ldx, y, ldy, rows, n, signs, inverse, s);
+    case 15: return launch_parts<15>(x, ldx, y, ldy, rows, n, signs, inverse, s);
     default: return hipErrorInvalidValue;
   }
 }

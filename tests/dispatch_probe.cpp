@@ -45,4 +45,8 @@ void gemm_plan_of(int64_t M, int64_t N, int64_t Kp, int epilogue, int64_t cus, i
   out[2] = p.split_k;
 }
 
+void launches_of(int64_t rows, int64_t units, int64_t most, int (*f)(int64_t, int64_t, int64_t, int64_t)) {
+  for_each_launch(rows, units, most, [&](int64_t r, int64_t nr, int64_t u, int64_t nu) { return f(r, nr, u, nu) != 0; });
+}
+
 }  // extern "C"

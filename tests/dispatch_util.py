@@ -27,6 +27,7 @@ def _rules():
     lib.gather_cols_rows_of.argtypes = [ctypes.c_int] + [i64] * 4
     lib.gather_rows_single_of.argtypes = [ctypes.c_int, ctypes.c_int] + [i64] * 4
     lib.gemm_plan_of.argtypes = [i64, i64, i64, ctypes.c_int, i64, ctypes.POINTER(i64)]
+    lib.launches_of.argtypes = [i64, i64, i64, ctypes.c_void_p]
     return lib
 
 
@@ -63,3 +64,16 @@ def gemm_plan(M, N, K, epilogue, cus=256):
     out = (i64 * 3)()
     _rules().gemm_plan_of(M, N, 64 * -(-K // 64), ("store", "accum", "unmask").index(epilogue), cus, out)
     return ("128", "64k", "64")[out[0]], out[1], out[2]
+
+
+def launches(rows, units, most, stop_after=None):
+    """(row0, rows, unit0, units) of each launch of at most ``most`` units."""
+    out = []
+
+    def note(*part):
+        out.append(part)
+        return stop_after is None or len(out) < stop_after
+
+    cb = ctypes.CFUNCTYPE(ctypes.c_int, i64, i64, i64, i64)(note)
+    _rules().launches_of(rows, units, most, ctypes.cast(cb, ctypes.c_void_p))
+    return out

@@ -2,7 +2,8 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import gather_cols, gather_rows_single, gemm_plan, gemv, mask_route, unmask_words
+from tests.dispatch_util import (gather_cols, gather_rows_single, gemm_plan, gemv, launches, mask_route,
+                                 unmask_words)
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -135,3 +136,24 @@ def test_tiled_products():
                 for epi in ("store", "accum"):
                     form, tiles, k = gemm_plan(M, N, K, epi)
                     assert k == 1 or (form == "128" and 0 < 2 * tiles < 256 and K >= 128 * k)
+
+
+@pytest.mark.parametrize("rows,units,most", [(5, 3, 100), (5, 3, 15), (5, 3, 14), (5, 3, 3), (5, 7, 3), (1, 1, 1), (4, 8, 7)])
+def test_launches_cover_the_rows_once(rows, units, most):
+    seen = set()
+    for r, nr, u, nu in launches(rows, units, most):
+        assert nr * nu <= most
+        part = {(i, j) for i in range(r, r + nr) for j in range(u, u + nu)}
+        assert len(part) == nr * nu and not part & seen
+        seen |= part
+    assert seen == {(i, j) for i in range(rows) for j in range(units)}
+
+
+def test_launches_of_long_rotations():
+    """2^22 blocks of 16384 on 1024 threads, 2^31 of 16 on four: past a launch."""
+    for rows, units, threads in ((2 ** 22, 1, 1024), (1, 2 ** 22, 1024), (2 ** 22, 512, 4), (3, 2 ** 30, 4)):
+        parts = launches(rows, units, MAX_THREADS // threads)
+        assert len(parts) > 1 and sum(nr * nu for _, nr, _, nu in parts) == rows * units
+        assert all(nr * nu * threads <= MAX_THREADS for _, nr, _, nu in parts)
+    assert launches(2 ** 20, 2, MAX_THREADS // 1024) == [(0, 2 ** 20, 0, 2)]
+    assert launches(10, 4, 4, stop_after=3)[-1] == (2, 1, 0, 4)

@@ -108,7 +108,8 @@ def test_mask_transposed(rows, cols, kind, dtype):
 
 def test_mask_more_rows_than_a_launch_has_workgroups():
     """2^24 rows and more: a workgroup per row would pass the launch limit of
-    2^32 threads, for ragged and for aligned rows."""
+    2^32 threads (and run the first few rows alone), for ragged and for aligned
+    rows."""
     for cols in (3, 4):
         rows = 2 ** 24 + 5
         x = torch.arange(rows * cols, dtype=torch.int32, device="cuda").reshape(rows, cols)
