@@ -82,7 +82,7 @@ mosaic_status mosaic_sample(const mosaic_rng* rng, int64_t rows, int64_t cols, u
   RngArgs a{};
   st = rng_args(rng, &a);
   if (st != MOSAIC_OK) return st;
-  if (rows > 0x7FFFFFFF) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
+  if (rows > kMaxGridThreads / 64) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
   return hip_status(launch_weighted_sample(a, rows, cols, out, ldo, out_dig, dig_pitch, (hipStream_t)stream),
                     "weighted sample launch");
 }
@@ -269,7 +269,8 @@ mosaic_status mosaic_rotate_quantize_mask(const float* x, int64_t ldx, int64_t r
     st = rng_args(noise, &na);
     if (st != MOSAIC_OK) return st;
   }
-  if (rows > 0x7FFFFFFF) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
+  if (rows > kMaxGridThreads / (lg <= 12 ? 256 : 256 << (lg - 12)))   // one workgroup per row
+    return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
   return hip_status(launch_rotate_quantize_mask(x, ldx, rows, n, lg, signs, qmax, u, ldu,
                                                 noise != nullptr ? &na : nullptr, out_dig, dig_pitch, scale,
                                                 (hipStream_t)stream), "rotate-quantize-mask launch");
@@ -283,7 +284,7 @@ mosaic_status mosaic_sparse_csr_count(const mosaic_rng* rng, int64_t rows, int64
   RngArgs a{};
   mosaic_status st = check_lpn_rng(rng, cols, &a);
   if (st != MOSAIC_OK) return st;
-  if (rows > 0x7FFFFFFF) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
+  if (rows > kMaxGridThreads / 64) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
   if (rng->dist == MOSAIC_DIST_WEIGHT)
     return hip_status(launch_weighted_csr_count(rows, a.row_weight, row_ptr, (hipStream_t)stream),
                       "weighted count launch");
@@ -300,7 +301,7 @@ mosaic_status mosaic_sparse_csr_fill(const mosaic_rng* rng, int64_t rows, int64_
   RngArgs a{};
   mosaic_status st = check_lpn_rng(rng, cols, &a);
   if (st != MOSAIC_OK) return st;
-  if (rows > 0x7FFFFFFF) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
+  if (rows > kMaxGridThreads / 64) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
   if (rng->dist == MOSAIC_DIST_WEIGHT)
     return hip_status(launch_weighted_csr_fill(a, rows, cols, row_ptr, col_idx, values, (hipStream_t)stream),
                       "weighted fill launch");
@@ -316,7 +317,7 @@ mosaic_status mosaic_sparse_gather_rows(int64_t rows, const int64_t* row_ptr, co
   if (row_ptr == nullptr || col_idx == nullptr || values == nullptr || d == nullptr || c == nullptr)
     return fail(MOSAIC_ERR_INVALID_ARG, "NULL operand");
   if (ldd < ncols || ldc < ncols) return fail(MOSAIC_ERR_INVALID_ARG, "leading dimension < ncols");
-  if (rows > 0x7FFFFFFF || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
+  if (rows > kMaxGridThreads / 256 || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
   return hip_status(launch_sparse_gather_rows(rows, row_ptr, col_idx, values, d, ldd, ncols, c, ldc, subtract != 0,
                                               (hipStream_t)stream), "sparse gather launch");
 }
@@ -331,7 +332,7 @@ mosaic_status mosaic_sparse_stream_gather_rows(const mosaic_rng* rng, int64_t ro
   RngArgs a{};
   mosaic_status st = check_lpn_rng(rng, rcols, &a);
   if (st != MOSAIC_OK) return st;
-  if (rows > 0x7FFFFFFF || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
+  if (rows > kMaxGridThreads / 256 || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
   return hip_status(launch_sparse_stream_gather_rows(a, rows, rcols, d, ldd, ncols, c, ldc, subtract != 0,
                                                      (hipStream_t)stream), "sparse gather launch");
 }
@@ -349,9 +350,15 @@ mosaic_status mosaic_sparse_gather_cols(int64_t M, int64_t N, const int64_t* row
     return fail(MOSAIC_ERR_INVALID_ARG, "y_f32 needs ldf >= N and both scale vectors");
   if (bias != nullptr && y_f32 == nullptr) return fail(MOSAIC_ERR_INVALID_ARG, "bias needs y_f32");
   if (M > 0x7FFFFFFF || (N + 31) / 32 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
-  const Dequant dq{s_rows, s_cols, bias, y_f32, ldf};
-  return hip_status(launch_sparse_gather_cols(M, N, row_ptr, col_idx, values, d, ldd, c, ldc, subtract != 0, dq,
-                                              (hipStream_t)stream), "sparse gather launch");
+  hipError_t e = hipSuccess;
+  for_each_launch(M, 1, kMaxGridThreads / 512, [&](int64_t r, int64_t rows, int64_t, int64_t) {
+    const Dequant dq{s_rows != nullptr ? s_rows + r : nullptr, s_cols, bias, y_f32 != nullptr ? y_f32 + r * ldf : nullptr,
+                     ldf};
+    e = launch_sparse_gather_cols(rows, N, row_ptr, col_idx, values, d + r * ldd, ldd, c + r * ldc, ldc, subtract != 0,
+                                  dq, (hipStream_t)stream);
+    return e == hipSuccess;
+  });
+  return hip_status(e, "sparse gather launch");
 }
 
 mosaic_status mosaic_count_mismatches(const uint32_t* a, int64_t lda, const uint32_t* b, int64_t ldb,
@@ -505,7 +512,7 @@ mosaic_status mosaic_hadamard28_rotate(const float* x, int64_t ldx, float* y, in
   if (ldx < n || ldy < n || ldx % 4 != 0 || ldy % 4 != 0)
     return fail(MOSAIC_ERR_INVALID_ARG, "ldx and ldy must be >= n and multiples of 4");
   if (signs != nullptr && !aligned16(signs)) return fail(MOSAIC_ERR_INVALID_ARG, "signs must be 16-byte aligned");
-  if (rows >= (int64_t(1) << 31)) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
+  if (rows > kMaxGridThreads / 256) return fail(MOSAIC_ERR_UNSUPPORTED, "too many rows");
   {
     const char* xb = (const char*)x;
     const char* xe = (const char*)(x + (rows - 1) * ldx + n);

@@ -14,7 +14,7 @@ mosaic_status mosaic_sparse_stream_gather_rows_terms(const mosaic_stream_term* t
   if (rows == 0 || ncols == 0 || nterms == 0) return MOSAIC_OK;
   if (terms == nullptr || c == nullptr) return fail(MOSAIC_ERR_INVALID_ARG, "NULL operand");
   if (ldc < ncols) return fail(MOSAIC_ERR_INVALID_ARG, "leading dimension < ncols");
-  if (rows > 0x7FFFFFFF || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
+  if (rows > kMaxGridThreads / 256 || (ncols + 63) / 64 > 65535) return fail(MOSAIC_ERR_UNSUPPORTED, "too large for one launch");
   StreamTerm t[MAX_TERMS];
   for (int l = 0; l < nterms; ++l) {
     if (terms[l].rcols < 0) return fail(MOSAIC_ERR_INVALID_ARG, "negative size");
@@ -52,9 +52,15 @@ mosaic_status mosaic_sparse_gather_cols_terms(const mosaic_sparse_term* terms, i
     if (x.cols < 0 || x.ldd < 0) return fail(MOSAIC_ERR_INVALID_ARG, "negative cols or ldd");
     t[l] = SparseTerm{x.row_ptr, x.col_idx, x.values, x.d, x.ldd, x.cols};
   }
-  const Dequant dq{s_rows, s_cols, bias, y_f32, ldf};
-  return hip_status(launch_sparse_gather_cols_terms(t, nterms, M, N, c, ldc, subtract != 0, dq, (hipStream_t)stream),
-                    "sparse gather launch");
+  hipError_t e = hipSuccess;
+  for_each_launch(M, 1, kMaxGridThreads / 512, [&](int64_t r, int64_t rows, int64_t, int64_t) {
+    for (int l = 0; l < nterms; ++l) t[l].d = terms[l].d + r * t[l].ldd;
+    const Dequant dq{s_rows != nullptr ? s_rows + r : nullptr, s_cols, bias, y_f32 != nullptr ? y_f32 + r * ldf : nullptr,
+                     ldf};
+    e = launch_sparse_gather_cols_terms(t, nterms, rows, N, c + r * ldc, ldc, subtract != 0, dq, (hipStream_t)stream);
+    return e == hipSuccess;
+  });
+  return hip_status(e, "sparse gather launch");
 }
 
 }  // extern "C"

@@ -88,6 +88,8 @@ inline MaskRoute mask_route(const MaskShape& a, int64_t cus) {
 // LDS a compute unit's up to 6144 columns. Device time, B beyond the last-level
 // cache.
 
+constexpr int64_t kGemvMaxN = 8 * (kMaxGridThreads / 256);   // a workgroup of 256 threads per 8 rows of B
+
 // Store: the matrix-core kernel clears C first (a launch of its own) and adds
 // partial sums. One row, matrix cores / dot products: 4096 x 1536 9.5 / 7.3 us,
 // 8192 x 3072 22.6 / 19.3, 1024 x 4096 7.4 / 7.0, 3072 x 5120 15.5 / 14.3; but 200 x 4096
@@ -95,7 +97,7 @@ inline MaskRoute mask_route(const MaskShape& a, int64_t cus) {
 // gain up to 2048 columns (8192 x 1536 13.9 / 12.3; 6656 x 4096 20.7 / 22.1) and
 // lose on many short rows sooner (16384 x 256 7.8 / 8.1, 28672 x 512 warm 13.4 / 13.8).
 inline bool gemv_takes_store(int64_t M, int64_t N, int64_t Kp) {
-  if (Kp <= 0 || N >= (int64_t(1) << 27) || (N > 8192 && Kp < 512)) return false;
+  if (Kp <= 0 || N > kGemvMaxN || (N > 8192 && Kp < 512)) return false;
   if (M == 2) return Kp <= 2048;
   return M == 1 && (Kp <= 3072 || (Kp <= 4096 && N >= 1024) || (Kp <= 6144 && N >= 3072));
 }
@@ -104,7 +106,7 @@ inline bool gemv_takes_store(int64_t M, int64_t N, int64_t Kp) {
 // x 6144 135 / 119; two rows: 4096 x 1536 9.6 / 8.6, 28672 x 2048 54 / 42. A single
 // chunk of 64 columns is behind with either: 16384 x 64 5.6 / 6.6 and 5.7 / 7.9.
 inline bool gemv_takes_unmask(int64_t M, int64_t N, int64_t Kp) {
-  if (Kp < 128 || N >= (int64_t(1) << 27)) return false;
+  if (Kp < 128 || N > kGemvMaxN) return false;
   return (M == 1 && Kp <= 6144) || (M == 2 && Kp <= 2048);
 }
 

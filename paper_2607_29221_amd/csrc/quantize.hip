@@ -183,12 +183,17 @@ void launch_quantize(const QuantizeLaunch& a, hipStream_t s) {
 hipError_t launch_quantize_rows(const float* x, int64_t ldx, int64_t rows, int64_t n, int32_t qmax, int32_t* q,
                                 int64_t ldq, int8_t* q_dig, int64_t q_pitch, float* scale, hipStream_t s) {
   if (rows == 0) return hipSuccess;
-  const QuantizeLaunch a{x, ldx, rows, n, qmax, q, ldq, q_dig, q_pitch, scale};
   // digits are 16-byte aligned in every row (checked by the caller)
   const bool aligned = n % 4 == 0 && ldx % 4 == 0 && ((uintptr_t)x & 15) == 0 &&
                        (q == nullptr || (ldq % 4 == 0 && ((uintptr_t)q & 15) == 0));
-  if (aligned) launch_quantize<false>(a, s);
-  else launch_quantize<true>(a, s);
+  // a workgroup per row, of 1024 threads at most
+  for_each_launch(rows, 1, kMaxGridThreads / 1024, [&](int64_t r, int64_t part, int64_t, int64_t) {
+    const QuantizeLaunch p{x + r * ldx, ldx, part, n, qmax, q != nullptr ? q + r * ldq : nullptr, ldq,
+                           q_dig != nullptr ? q_dig + r * q_pitch : nullptr, q_pitch, scale != nullptr ? scale + r : nullptr};
+    if (aligned) launch_quantize<false>(p, s);
+    else launch_quantize<true>(p, s);
+    return hipPeekAtLastError() == hipSuccess;
+  });
   return hipGetLastError();
 }
 

@@ -70,10 +70,12 @@ def test_products_of_one_or_two_rows():
     for M, N, K in ((1, 4096, 1536), (1, 1024, 4096), (1, 3072, 6144), (1, 64, 3072), (2, 8192, 2048), (1, 28672, 512),
                     (1, 8192, 64)):
         assert gemv(M, N, K, unmask=False)
-    for M, N, K in ((1, 28672, 64), (2, 4096, 64), (1, 64, 6208), (2, 64, 2112), (3, 64, 128), (1, 2 ** 27, 128)):
+    for M, N, K in ((1, 28672, 64), (2, 4096, 64), (1, 64, 6208), (2, 64, 2112), (3, 64, 128), (1, 2 ** 27 - 7, 128)):
         assert not gemv(M, N, K, unmask=True)
     for M, N, K in ((1, 64, 65), (1, 28672, 6144), (2, 16384, 2048)):
         assert gemv(M, N, K, unmask=True)
+    for unmask in (False, True):        # a workgroup of 256 threads per 8 rows of B
+        assert gemv(1, 2 ** 27 - 8, 512, unmask) and not gemv(1, 2 ** 27 - 7, 512, unmask)
 
 
 def test_unmask_from_words():

@@ -138,3 +138,17 @@ def test_mask_many_short_rows(rows, cols, kind):
     assert np.array_equal(got[:, 1: 1 + cols], want)
     assert np.all(got[:, 0] == 77) and np.all(got[:, 1 + cols:] == 77)
     assert np.array_equal(unpack_digits(dig), want) and pad_is_zero(dig)
+
+
+@pytest.mark.parametrize("n", [3, 4])
+def test_quantize_more_rows_than_a_launch_has_workgroups(n):
+    """The codes, digits and scales of 2^24 rows and more are those of their parts."""
+    rows, cut = 2 ** 24 + 5, 2 ** 21 + 1
+    x = torch.empty((rows, n), device="cuda").normal_()
+    q, sc = torch.zeros((rows, n), dtype=torch.int32, device="cuda"), torch.zeros(rows, device="cuda")
+    m.mosaic_quantize_rows(x, 1997, q=q, scale=sc)
+    for r in range(0, rows, cut):
+        k = min(cut, rows - r)
+        qp, sp = torch.empty((k, n), dtype=torch.int32, device="cuda"), torch.empty(k, device="cuda")
+        m.mosaic_quantize_rows(x[r: r + k], 1997, q=qp, scale=sp)
+        assert torch.equal(q[r: r + k], qp) and torch.equal(sc[r: r + k], sp)

@@ -93,3 +93,17 @@ def test_gather_cols_terms_rows_that_overlap(M, stride):
         m.mosaic_sparse_gather_cols_terms([(p, d)], M, got)
         m.mosaic_sparse_gather_cols(p, d.contiguous(), M, want)
         assert torch.equal(got, want)
+
+
+def test_gather_cols_more_rows_than_a_launch_has_threads():
+    """2^23 rows of d and more go in several launches, in the single gather too."""
+    M, N, cols = 2 ** 24 + 9, 2, 600
+    p = m.mosaic_sparse_csr(m.rng(8, 0x61, 3, m.DIST_SPARSE, log2_inv_density=3), N, cols)
+    row = to_dev_ring(np.random.default_rng(4).integers(0, 2 ** 32, (1, cols + 8), dtype=np.uint32))[0]
+    d = row.as_strided((M, cols), (0, 1))
+    want = torch.zeros((1, N), dtype=torch.int32, device="cuda")
+    m.mosaic_sparse_gather_cols(p, d[:1], 1, want)
+    for call in (lambda c: m.mosaic_sparse_gather_cols_terms([(p, d)], M, c), lambda c: m.mosaic_sparse_gather_cols(p, d, M, c)):
+        c = torch.zeros((M, N), dtype=torch.int32, device="cuda")
+        call(c)
+        assert torch.equal(c, want.expand(M, N))
