@@ -7,11 +7,14 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <memory>
 
 #include "../include/mosaic.h"
 #include "../include/mosaic_probe.h"
 
 extern int g_launches;
+extern bool g_terms;
+extern int64_t g_sum;
 
 static int g_fail = 0;
 #define EXPECT(call, want)                                                                   \
@@ -153,6 +156,113 @@ int main() {
                                    nullptr), INV);     // ldf < N
   EXPECT(mosaic_sparse_gather_cols(4, 4, Fl, (int32_t*)F, Fu, Fu, 4, Fu, 4, 0, nullptr, nullptr, Ff, nullptr, 0,
                                    nullptr), INV);     // bias without y_f32
+  // over several matrices; the arrays hold exactly as many terms as are passed
+  const auto streams = [&](int n) {
+    std::unique_ptr<mosaic_stream_term[]> t(new mosaic_stream_term[n]);
+    for (int l = 0; l < n; ++l) t[l] = mosaic_stream_term{w, 8, Fu, 4};
+    return t;
+  };
+  const auto matrices = [&](int n) {
+    std::unique_ptr<mosaic_sparse_term[]> t(new mosaic_sparse_term[n]);
+    for (int l = 0; l < n; ++l) t[l] = mosaic_sparse_term{Fl, (int32_t*)F, Fu, 8, Fu, 8};
+    return t;
+  };
+  const auto rows_terms = [&](const mosaic_stream_term* t, int32_t n, int64_t rows = 4, int64_t ncols = 4,
+                              uint32_t* c = (uint32_t*)(uintptr_t)(1u << 20), int64_t ldc = 4) {
+    return mosaic_sparse_stream_gather_rows_terms(t, n, rows, ncols, c, ldc, 0, nullptr);
+  };
+  const auto cols_terms = [&](const mosaic_sparse_term* t, int32_t n, int64_t M = 4, int64_t N = 4, int64_t ldc = 4,
+                              const float* sr = nullptr, const float* sc = nullptr, const float* bias = nullptr,
+                              float* y = nullptr, int64_t ldf = 0) {
+    return mosaic_sparse_gather_cols_terms(t, n, M, N, Fu, ldc, 0, sr, sc, bias, y, ldf, nullptr);
+  };
+  const auto t4 = streams(4);
+  for (int32_t n : {-1, 5, INT32_MAX, INT32_MIN}) {
+    EXPECT(rows_terms(t4.get(), n), INV);
+    EXPECT(cols_terms(matrices(4).get(), n), INV);
+  }
+  EXPECT(cols_terms(matrices(1).get(), 0), INV);
+  EXPECT(rows_terms(nullptr, 0), OK);
+  EXPECT(rows_terms(nullptr, 2), INV);
+  EXPECT(cols_terms(nullptr, 2), INV);
+  EXPECT(rows_terms(t4.get(), 4, -1), INV);
+  EXPECT(rows_terms(t4.get(), 4, 4, -1), INV);
+  EXPECT(rows_terms(t4.get(), 4, 0), OK);
+  EXPECT(rows_terms(t4.get(), 4, 4, 0), OK);
+  EXPECT(rows_terms(t4.get(), 4, 4, 4, nullptr), INV);
+  EXPECT(rows_terms(t4.get(), 4, 4, 4, Fu, 3), INV);
+  EXPECT(rows_terms(t4.get(), 4, int64_t(1) << 24), UNS);
+  EXPECT(rows_terms(t4.get(), 4, 4, int64_t(1) << 22, Fu, int64_t(1) << 22), UNS);
+  for (int l = 0; l < 4; ++l) {                       // each term's own checks, wherever it stands
+    auto t = streams(l + 1);
+    t[l].rcols = -1;
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].rcols = 4;                                   // t = 5 entries in 4 columns
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].rcols = 8193;
+    EXPECT(rows_terms(t.get(), l + 1), UNS);
+    t[l].rcols = 8;
+    t[l].ldd = 3;
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].ldd = 4;
+    t[l].d = nullptr;
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].d = Fu;
+    t[l].rng = u;                                     // not SPARSE/WEIGHT
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].rng = sp;                                    // density 2^-32
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].rng = w;
+    t[l].rng.transposed = 1;
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+    t[l].rng = w;
+    t[l].rng.row_weight = -1;
+    EXPECT(rows_terms(t.get(), l + 1), INV);
+
+    auto c = matrices(l + 1);
+    c[l].cols = -1;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+    c[l].cols = 8;
+    c[l].ldd = -1;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+    c[l].ldd = 8;
+    c[l].row_ptr = nullptr;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+    c[l].row_ptr = Fl;
+    c[l].col_idx = nullptr;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+    c[l].col_idx = (int32_t*)F;
+    c[l].values = nullptr;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+    c[l].values = Fu;
+    c[l].d = nullptr;
+    EXPECT(cols_terms(c.get(), l + 1), INV);
+  }
+  const auto m2 = matrices(2);
+  EXPECT(cols_terms(m2.get(), 2, -1), INV);
+  EXPECT(cols_terms(m2.get(), 2, 4, -1), INV);
+  EXPECT(cols_terms(m2.get(), 2, 0), OK);
+  EXPECT(cols_terms(m2.get(), 2, 4, 0), OK);
+  EXPECT(cols_terms(m2.get(), 2, 4, 4, 3), INV);
+  EXPECT(cols_terms(m2.get(), 2, 4, 4, 4, nullptr, Ff, nullptr, Ff, 4), INV);
+  EXPECT(cols_terms(m2.get(), 2, 4, 4, 4, Ff, nullptr, nullptr, Ff, 4), INV);
+  EXPECT(cols_terms(m2.get(), 2, 4, 4, 4, Ff, Ff, nullptr, Ff, 3), INV);
+  EXPECT(cols_terms(m2.get(), 2, 4, 4, 4, nullptr, nullptr, Ff), INV);                // bias without y_f32
+  EXPECT(cols_terms(m2.get(), 2, 4, 32 * 65535 + 1, 32 * 65535 + 1), UNS);
+  EXPECT(cols_terms(m2.get(), 2, int64_t(1) << 31), UNS);
+  g_terms = true;                                      // accepted: every term is copied and handed on
+  for (int n = 1; n <= 4; ++n) {
+    g_sum = 0;
+    EXPECT(rows_terms(streams(n).get(), n), OK);
+    EXPECT(g_sum, n * (8 + 4 + 5));
+    g_sum = 0;
+    EXPECT(cols_terms(matrices(n).get(), n, 4, 4, 4, Ff, Ff, Ff, Ff, 4), OK);
+    EXPECT(g_sum, n * 16 + 4);
+  }
+  g_sum = 0;                                           // rows in several launches
+  EXPECT(cols_terms(m2.get(), 2, (int64_t(1) << 24) + 1), OK);
+  EXPECT(g_sum, (int64_t(1) << 24) + 1 + 3 * 32);
+  g_terms = false;
   EXPECT(mosaic_count_mismatches(Fu, 4, Fu, 4, 4, 4, nullptr, nullptr), INV);
   EXPECT(mosaic_count_mismatches(Fu, 3, Fu, 4, 4, 4, Fl, nullptr), INV);
   int64_t ops = 0;

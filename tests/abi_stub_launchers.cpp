@@ -1,10 +1,14 @@
 // Host-only stand-ins for the kernel launchers of libmosaic, linked with the
-// ABI layer (abi.cpp) in the sanitizer build of tests/test_abi_sanitize.py.
+// ABI layer (abi.cpp, abi_terms.cpp) in the sanitizer build of tests/test_abi_sanitize.py.
 // The driver only makes calls that validation must reject, so any launcher
-// reached is a failure: each one counts the call and reports an error.
+// reached is a failure: each one counts the call and reports an error. The
+// launchers of the gathers over several matrices are reached on purpose (g_terms
+// true): they check what they are handed.
 #include "../paper_2607_29221_amd/csrc/internal.h"
 
 int g_launches = 0;
+bool g_terms = false;          // a call that launches is under way
+int64_t g_sum = 0;             // of the sizes handed on, so that every copied term is read
 
 namespace mosaic {
 #define STUB { ++g_launches; return hipErrorInvalidValue; }
@@ -45,5 +49,18 @@ hipError_t launch_rotate_quantize_mask(const float*, int64_t, int64_t, int64_t, 
                                        hipStream_t) STUB
 hipError_t launch_quantize_rows(const float*, int64_t, int64_t, int64_t, int32_t, int32_t*, int64_t, int8_t*,
                                 int64_t, float*, hipStream_t) STUB
+hipError_t launch_sparse_stream_gather_rows_terms(const StreamTerm* t, int n, int64_t, int64_t, uint32_t*, int64_t, int,
+                                                  hipStream_t) {
+  if (!g_terms) STUB
+  for (int l = 0; l < n; ++l) g_sum += t[l].rcols + t[l].ldd + t[l].r.row_weight;
+  return hipSuccess;
+}
+hipError_t launch_sparse_gather_cols_terms(const SparseTerm* t, int n, int64_t M, int64_t, uint32_t*, int64_t, int,
+                                           const Dequant&, hipStream_t) {
+  if (!g_terms) STUB
+  for (int l = 0; l < n; ++l) g_sum += t[l].cols + t[l].ldd;
+  g_sum += M;
+  return hipSuccess;
+}
 #undef STUB
 }  // namespace mosaic

@@ -1,5 +1,5 @@
 """Sanitizer builds on the CPU (no GPU): the ABI layer's argument validation
-(abi.cpp, host code only, kernel launchers replaced by stubs that must never
+(abi.cpp and abi_terms.cpp, host code only, kernel launchers replaced by stubs that must never
 be reached) and the oracle's C leg, each built with AddressSanitizer and
 UndefinedBehaviorSanitizer and run on inputs that exercise every rejection
 path, zero-sized calls and the host-side threshold computation."""
@@ -27,7 +27,8 @@ def test_abi_validation_under_sanitizers(tmp_path):
     if not os.path.exists(HIPCC):
         pytest.skip("hipcc not available")
     objs = []
-    for src in ("paper_2607_29221_amd/csrc/abi.cpp", "tests/abi_stub_launchers.cpp", "tests/abi_sanitize_driver.cpp"):
+    for src in ("paper_2607_29221_amd/csrc/abi.cpp", "paper_2607_29221_amd/csrc/abi_terms.cpp",
+                "tests/abi_stub_launchers.cpp", "tests/abi_sanitize_driver.cpp"):
         obj = str(tmp_path / (os.path.basename(src) + ".o"))
         _run([HIPCC, "-x", "hip", "--cuda-host-only", "-std=c++17", "-O1", "-g"] + SAN +
              ["-c", os.path.join(ROOT, src), "-o", obj], str(tmp_path))
