@@ -129,9 +129,8 @@ def test_masked_matmul(M, N, K):
                                    (300, 4099, 640)])
 def test_masked_matmul_mid_size(M, N, K):
     """Tiled-kernel products with fewer tiles than compute units and a long
-    K range, checked in full: the tiles run as split-K pieces added
-    atomically after a clear of their outputs (2-8 pieces; N = 1001 and 4099
-    take the one-word epilogue paths, 65 x 130 x 512 the smallest pieces)."""
+    K range, checked in full: 64-row tiles whose stages two groups of waves
+    share (N = 1001 and 4099 take the epilogue of unaligned rows)."""
     rng = _rng_np(M + N + K)
     a = _random_ring(rng, (M, K), edge=True)
     b = _random_ring(rng, (N, K), edge=True)
@@ -155,10 +154,8 @@ def test_masked_matmul_stage_loop_forms(K):
 
 
 def test_masked_matmul_split_output_window():
-    """Split-K pieces writing into a window of a wider C (ldc > N, a column
-    offset): the clear before a store and the atomic adds touch only the
-    window; K past one launch's range makes the second chunk accumulate, in
-    two pieces per tile."""
+    """A product into a window of a wider C (ldc > N, a column offset); K past
+    one launch's range makes the second chunk accumulate."""
     M, N, K = 150, 203, 33000
     rng = _rng_np(5)
     a = _random_ring(rng, (M, K))
@@ -203,8 +200,8 @@ def test_masked_matmul_short_a_many_tiles(M, N, K):
 
 @pytest.mark.parametrize("M,N,K", [(1, 1000, 4160), (64, 700, 1024), (200, 300, 512)])
 def test_masked_matmul_graph_replay(M, N, K):
-    """The product captured in a HIP graph (decode kernel: C cleared by a
-    kernel, partial products added atomically; tiled kernel) and replayed
+    """The product captured in a HIP graph (dot products; decode kernel: C
+    cleared by a kernel, partial products added atomically; tiled kernel) and replayed
     three times, with C overwritten and other work run eagerly between the
     replays: every replay equals the eagerly launched product."""
     rng = _rng_np(M + 3 * N + 7 * K)
@@ -241,8 +238,8 @@ def test_masked_matmul_accumulator_extreme_short_a(M):
 
 @pytest.mark.parametrize("M,N,K", [(70, 50, 40000), (130, 132, 33000), (3, 37, 65600)])
 def test_masked_matmul_long_inner_dimension(M, N, K):
-    """K >= 2^15 runs as chunks added into C (tiled kernel, per-word and
-    16-byte epilogues, and the K-split kernel)."""
+    """K >= 2^15 runs as chunks added into C (tiled kernel, epilogues of
+    unaligned and aligned rows, and the K-split kernel)."""
     rng = _rng_np(M + N + K)
     a = _random_ring(rng, (M, K), edge=True)
     b = _random_ring(rng, (N, K), edge=True)
@@ -550,7 +547,7 @@ def test_unmask_in_place_tiled(M, target):
 
 def _bias(N, kind, seed):
     """None, a 16-byte aligned bias, or one at a 4-byte offset (the tiled
-    kernel's epilogue then takes its one-word path)."""
+    kernel then takes its epilogue of unaligned rows)."""
     if kind is None:
         return None, 0.0
     b = torch.from_numpy(_rng_np(seed).standard_normal(N + 1).astype(np.float32)).cuda()
