@@ -130,7 +130,9 @@ def test_masked_matmul(M, N, K):
 def test_masked_matmul_mid_size(M, N, K):
     """Tiled-kernel products with fewer tiles than compute units and a long
     K range, checked in full: 64-row tiles whose stages two groups of waves
-    share (N = 1001 and 4099 take the epilogue of unaligned rows)."""
+    share, and 128-row tiles in eight pieces along K added atomically after a
+    clear of their outputs (K = 4096); N = 1001 and 4099 take the epilogue of
+    unaligned rows."""
     rng = _rng_np(M + N + K)
     a = _random_ring(rng, (M, K), edge=True)
     b = _random_ring(rng, (N, K), edge=True)
@@ -154,8 +156,10 @@ def test_masked_matmul_stage_loop_forms(K):
 
 
 def test_masked_matmul_split_output_window():
-    """A product into a window of a wider C (ldc > N, a column offset); K past
-    one launch's range makes the second chunk accumulate."""
+    """Split-K pieces writing into a window of a wider C (ldc > N, a column
+    offset): the clear before a store and the atomic adds touch only the
+    window; K past one launch's range makes the second chunk accumulate, in
+    64-row tiles."""
     M, N, K = 150, 203, 33000
     rng = _rng_np(5)
     a = _random_ring(rng, (M, K))
