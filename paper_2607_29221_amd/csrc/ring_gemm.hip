@@ -89,6 +89,7 @@ struct Form {
   static constexpr int NL = 2 + RB / 8;          // direct loads per wave per stage
   static constexpr int UN = NST % 2 ? 2 * NST : NST;   // stages per iteration of the steady loop
   static_assert(KW * GRP <= 160 * 1024 && BM * (BN + 4) * 4 <= KW * GRP, "LDS");
+  static_assert(NST >= 2 && NST <= 4, "wait_loads");
 };
 
 struct Tile {
@@ -151,12 +152,11 @@ __device__ __forceinline__ void wait_vm() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// At most n stages of this wave's NL direct loads each may still be in flight.
+// At most n stages of this wave's NL direct loads each may still be in flight
+// (n <= NST - 1 <= 3).
 template <int NL>
 __device__ __forceinline__ void wait_loads(int n) {
-  if (n >= 5) wait_vm<5 * NL>();
-  else if (n == 4) wait_vm<4 * NL>();
-  else if (n == 3) wait_vm<3 * NL>();
+  if (n >= 3) wait_vm<3 * NL>();
   else if (n == 2) wait_vm<2 * NL>();
   else if (n == 1) wait_vm<NL>();
   else wait_vm<0>();
@@ -422,11 +422,13 @@ __global__ __launch_bounds__(F::NT, 2) void ring_gemm_kernel(GemmLaunch g) {
   // epilogue: recombine the shift classes and write. Output layout of the
   // 32 x 32 MFMA: register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4,
   // column l % 32.
-  // Recombine the shift classes and stage the 128 x 128 tile in LDS (rows
+  // Recombine the shift classes and stage the BM x 128 tile in LDS (rows
   // padded to 132 words so the two rows a wave writes per instruction fall in
-  // different banks), then write it out in 16-byte chunks along rows: thread
-  // t takes chunks t + 512 k (row c / 32, columns 4 (c % 32) .. + 3), so each
-  // wave instruction covers two whole 512-byte tile rows. All loads of the
+  // different banks; with two groups of waves the second adds to what the
+  // first stored), then write it out in 16-byte chunks along rows: thread t
+  // takes chunks t + NT k (row c / 32, columns 4 (c % 32) .. + 3), so each wave
+  // instruction covers two whole 512-byte tile rows. A piece of a split tile
+  // is added word by word instead (gemm_tile_atomic_add). All loads of the
   // unmask epilogue (Y', K_c, scales) are issued before its first store.
   __builtin_amdgcn_s_barrier();                 // every wave is done reading stage data
   uint32_t* ctile = (uint32_t*)lds_all;

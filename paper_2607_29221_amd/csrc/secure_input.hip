@@ -252,8 +252,10 @@ hipError_t launch_rotate_quantize_mask(const float* x, int64_t ldx, int64_t rows
   if (rows == 0) return hipSuccess;
   if (signs != nullptr && u != nullptr) {
     // rows that fit in registers, for the block counts that a length whose
-    // largest power of two is b has: one launch (ROW: log2 b, blocks, blocks per
-    // LDS pass: all of them while their LDS leaves six waves per SIMD, else one).
+    // largest power of two is b has, and 8 of 1024 and 2 of 4096: one launch (ROW:
+    // log2 b, blocks, blocks that pass through LDS at a time, a divisor of the
+    // blocks: a pass costs barriers, its LDS resident workgroups; as listed four
+    // to eight waves per SIMD fit).
     // Not 7 blocks of 2048: with 14 groups of noise in straight-line code the
     // compiler copied the noise parameters to scratch memory (138 us for 2048
     // rows against 90 in two launches).

@@ -20,6 +20,9 @@
 // ten entries each in flight. Gathers from the L2 instead, one request per
 // entry and row of d, and the levels one after the other took 30 us for 8 rows
 // against 2 x 14336 rows of 80 entries; this kernel 12 us.
+//
+// Where the gathers of one matrix (sparse.hip) are ahead they run instead, one
+// matrix after the other: gather_rows_single and gather_cols_rows.
 #include "sparse_common.h"
 
 namespace mosaic {
@@ -46,7 +49,9 @@ template <int COLS>
 __global__ __launch_bounds__(256) void gather_stream_terms_kernel(DrawTerms a, int64_t ncols, uint32_t* c,
                                                                   int64_t ldc, int subtract) {
   constexpr int LPG = COLS / 4, G = 256 / LPG;        // lanes per group, groups
-  constexpr int U = COLS == 256 ? INFLIGHT : 3;       // a row of 24 entries has 1 or 2 per group of 16
+  // entries in flight per lane; of the 16 groups at 64 columns a row of 24
+  // entries gives each 1 or 2, one of 80 five, in two turns
+  constexpr int U = COLS == 256 ? INFLIGHT : 3;
   extern __shared__ uint32_t lds[];
   __shared__ int count[MAX_TERMS];
   __shared__ u32x4 part[G - 1][LPG];
