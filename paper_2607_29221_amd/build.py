@@ -67,7 +67,8 @@ def binding_digest() -> str:
     h = hashlib.sha256()
     h.update(" ".join(BINDING_FLAGS + [HIPCC, torch.__version__, str(torch._C._GLIBCXX_USE_CXX11_ABI),
                                        sysconfig.get_config_var("SOABI") or sys.version]).encode())
-    for path in (os.path.join(CSRC, "binding.cpp"), os.path.join(INCLUDE, "mosaic.h")):
+    for path in (os.path.join(CSRC, "binding.cpp"), os.path.join(CSRC, "dispatch.h"),
+                 os.path.join(INCLUDE, "mosaic.h")):
         with open(path, "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -14,6 +14,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/mosaic.h"
+#include "dispatch.h"
 
 namespace {
 
@@ -28,6 +29,7 @@ struct Abi {
   decltype(&mosaic_rotate_quantize_mask) rotate_quantize_mask;
   decltype(&mosaic_sparse_stream_gather_rows_terms) stream_terms;
   decltype(&mosaic_sparse_gather_cols_terms) cols_terms;
+  decltype(&mosaic_sparse_gather_cols) gather_cols;
   decltype(&mosaic_hadamard_rotate) hadamard_rotate;
   decltype(&mosaic_quantize_rows) quantize_rows;
 } abi;
@@ -381,11 +383,12 @@ FUNCTION(stream_terms, 5) {
   });
 }
 
-bool attr_ptr(PyObject* o, PyObject* name, at::ScalarType dt, const void** p) {
+bool attr_ptr(PyObject* o, PyObject* name, at::ScalarType dt, const void** p, int64_t* n = nullptr) {
   PyObject* v = PyObject_GetAttr(o, name);
   const at::Tensor* t = v != nullptr ? plain(v) : nullptr;
   const bool ok = t != nullptr && t->dim() == 1 && t->scalar_type() == dt && t->stride(0) == 1;
   if (ok) *p = t->data_ptr();
+  if (ok && n != nullptr) *n = t->size(0);
   Py_XDECREF(v);
   PyErr_Clear();
   return ok && *p != nullptr;
@@ -402,7 +405,7 @@ bool attr_size(PyObject* o, PyObject* name, int64_t* n) {
 // (terms, M, c, subtract, y_f32, s_rows, s_cols, bias); a term is a tuple
 // (SparseRows, d)
 FUNCTION(cols_terms, 8) {
-  int64_t M, N = 0;
+  int64_t M, N = 0, all_cols = 0, all_entries = 0;
   int32_t subtract;
   void* s;
   NEED(PyList_CheckExact(a[0]) && size(a[1], &M));
@@ -413,20 +416,35 @@ FUNCTION(cols_terms, 8) {
     PyObject* t = PyList_GET_ITEM(a[0], l);
     NEED(PyTuple_CheckExact(t) && PyTuple_GET_SIZE(t) == 2);
     PyObject* p = PyTuple_GET_ITEM(t, 0);
-    int64_t rows, cols;
+    int64_t rows, cols, capacity = 0;
     const void *rp, *ci, *va;
     Mat d;
     NEED(attr_size(p, s_rows, &rows) && attr_size(p, s_cols, &cols) && (l == 0 || rows == N));
     N = rows;
     NEED(attr_ptr(p, s_row_ptr, at::kLong, &rp) && attr_ptr(p, s_col_idx, at::kInt, &ci) &&
-         attr_ptr(p, s_values, at::kInt, &va) && matrix(PyTuple_GET_ITEM(t, 1), M, cols, at::kInt, false, &d));
+         attr_ptr(p, s_values, at::kInt, &va, &capacity) && matrix(PyTuple_GET_ITEM(t, 1), M, cols, at::kInt, false, &d));
     terms[l] = mosaic_sparse_term{(const int64_t*)rp, (const int32_t*)ci, (const uint32_t*)va, cols,
                                   (const uint32_t*)d.p, d.ld};
+    all_cols += cols;
+    all_entries += capacity / rows;     // the arrays hold at least the entries
   }
   Mat c, f, sr, sc, bias;
   NEED(matrix(a[2], M, N, at::kInt, false, &c) && matrix(a[4], M, N, at::kFloat, true, &f) &&
        vec(a[5], M, at::kFloat, !f.given(), &sr) && vec(a[6], N, at::kFloat, !f.given(), &sc) &&
        vec(a[7], N, at::kFloat, true, &bias) && truth(a[3], &subtract) && current_stream(&s));
+  if (mosaic::gather_cols_sparse((int)n, M, N, all_cols, all_entries))
+    return status([&] {
+      for (Py_ssize_t l = 0; l < n; ++l) {
+        const mosaic_sparse_term& t = terms[l];
+        const bool last = l + 1 == n;     // which also writes the dequantised output
+        const mosaic_status st = abi.gather_cols(
+            M, N, t.row_ptr, t.col_idx, t.values, t.d, t.ldd, (uint32_t*)c.p, c.ld, subtract,
+            last ? (const float*)sr.p : nullptr, last ? (const float*)sc.p : nullptr,
+            last ? (const float*)bias.p : nullptr, last ? (float*)f.p : nullptr, last ? f.ld : 0, s);
+        if (st != MOSAIC_OK) return st;
+      }
+      return MOSAIC_OK;
+    });
   return status([&] {
     return abi.cols_terms(terms, (int32_t)n, M, N, (uint32_t*)c.p, c.ld, subtract, (const float*)sr.p,
                           (const float*)sc.p, (const float*)bias.p, (float*)f.p, f.ld, s);

@@ -247,6 +247,20 @@ inline int gather_cols_rows(int nterms, int64_t M, int64_t N, int64_t cols, int6
   return mb;
 }
 
+// The same choice where the entries are known too (the binding holds the arrays;
+// the call over several matrices sees device pointers alone): true for the
+// matrices one after the other. `entries`: per row, of all n matrices; cols: the
+// sum of theirs. Gathered from memory an output costs its entries, staged a part
+// of the copy of d's rows and a fixed part besides: from memory / staged, 1536
+// columns of 4 entries 64 x 8192 9.3 / 21.9 us, of 8 16 x 28672 8.6 / 18.5, of 12 39 /
+// 58 for 64 x 28672, of 24 72 / 62; 1024 columns of 16 12.3 / 17.6 for 16 x 28672.
+// Several matrices cost a launch each, 2.5 us (24 and 16 entries, 16 x 14336: 20.1 /
+// 16.4; twice 8, 10.4 / 16.6).
+inline bool gather_cols_sparse(int n, int64_t M, int64_t N, int64_t cols, int64_t entries) {
+  if (cols > 2048 * (int64_t)n || (n > 1 && M * N <= 64 * 1024)) return false;
+  return entries < 12 * n + cols / 200;
+}
+
 // Row gathers whose rows are drawn inside the call (rows x ncols outputs, n
 // matrices, `entries` in a row of all of them, `weight`: the first is a WEIGHT
 // stream): true for the matrices one after the other by gather_rows_kernel, one

@@ -43,7 +43,7 @@ def _check(status: int, name: str) -> None:
 # Entry points that _binding.so calls, in the order it expects.
 _BOUND = ("mosaic_sample", "mosaic_mask", "mosaic_masked_matmul", "mosaic_integrity_check", "mosaic_unmask",
           "mosaic_unmask_words", "mosaic_rotate_quantize_mask", "mosaic_sparse_stream_gather_rows_terms",
-          "mosaic_sparse_gather_cols_terms", "mosaic_hadamard_rotate", "mosaic_quantize_rows")
+          "mosaic_sparse_gather_cols_terms", "mosaic_sparse_gather_cols", "mosaic_hadamard_rotate", "mosaic_quantize_rows")
 _b = None
 
 

@@ -33,6 +33,10 @@ int gather_cols_rows_of(int nterms, int64_t M, int64_t N, int64_t cols, int64_t 
   return gather_cols_rows(nterms, M, N, cols, cus);
 }
 
+int gather_cols_sparse_of(int n, int64_t M, int64_t N, int64_t cols, int64_t entries) {
+  return gather_cols_sparse(n, M, N, cols, entries);
+}
+
 int gather_rows_single_of(int n, int weight, int64_t entries, int64_t rows, int64_t ncols, int64_t cus) {
   return gather_rows_single(n, weight != 0, entries, rows, ncols, cus);
 }

@@ -25,6 +25,7 @@ def _rules():
     lib.gemv_takes.argtypes = [i64, i64, i64, ctypes.c_int]
     lib.unmask_words_form_of.argtypes = [i64] * 4
     lib.gather_cols_rows_of.argtypes = [ctypes.c_int] + [i64] * 4
+    lib.gather_cols_sparse_of.argtypes = [ctypes.c_int] + [i64] * 4
     lib.gather_rows_single_of.argtypes = [ctypes.c_int, ctypes.c_int] + [i64] * 4
     lib.gemm_plan_of.argtypes = [i64, i64, i64, ctypes.c_int, i64, ctypes.POINTER(i64)]
     lib.launches_of.argtypes = [i64, i64, i64, ctypes.c_void_p]
@@ -51,6 +52,11 @@ def unmask_words(M, N, K, cus=256):
 def gather_cols(nterms, M, N, cols, cus=256):
     """Rows of d staged per workgroup, 0 if they are read from memory."""
     return _rules().gather_cols_rows_of(nterms, M, N, cols, cus)
+
+
+def gather_cols_sparse(n, M, N, cols, entries):
+    """Whether a column gather of known entries runs its matrices one after the other."""
+    return bool(_rules().gather_cols_sparse_of(n, M, N, cols, entries))
 
 
 def gather_rows_single(n, weight, entries, rows, ncols, cus=256):

@@ -2,8 +2,8 @@
 limits (no GPU needed)."""
 import pytest
 
-from tests.dispatch_util import (gather_cols, gather_rows_single, gemm_plan, gemv, launches, mask_route,
-                                 unmask_words)
+from tests.dispatch_util import (gather_cols, gather_cols_sparse, gather_rows_single, gemm_plan, gemv, launches,
+                                 mask_route, unmask_words)
 
 MAX_THREADS = 2 ** 32 - 256
 
@@ -102,6 +102,17 @@ def test_column_gathers():
         for N in (1, 33, 8192, 8193, 10 ** 6):
             for cols in (1, 513, 2560, 2561, 5121, 8192, 20480, 20481):
                 assert 4 * cols * gather_cols(2, M, N, cols) <= 80 * 1024
+
+
+def test_column_gathers_of_few_entries():
+    """Staging d's rows for a few entries per row took up to twice the single
+    gather's time."""
+    for n, M, N, cols, entries in ((1, 64, 8192, 1536, 4), (1, 1, 1024, 1536, 12), (1, 64, 14336, 1024, 16),
+                                   (2, 64, 8192, 2560, 8)):
+        assert gather_cols_sparse(n, M, N, cols, entries)
+    for n, M, N, cols, entries in ((1, 64, 8192, 1536, 24), (1, 64, 14336, 1536, 20), (2, 64, 28672, 2560, 40),
+                                   (2, 8, 8192, 2560, 8), (2, 16, 14336, 2560, 160), (1, 64, 8192, 4096, 4)):
+        assert not gather_cols_sparse(n, M, N, cols, entries)
 
 
 def test_row_gathers():

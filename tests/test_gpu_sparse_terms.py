@@ -107,3 +107,27 @@ def test_gather_cols_more_rows_than_a_launch_has_threads():
         c = torch.zeros((M, N), dtype=torch.int32, device="cuda")
         call(c)
         assert torch.equal(c, want.expand(M, N))
+
+
+@pytest.mark.parametrize("levels", [1, 2])
+def test_gather_cols_terms_of_few_entries(levels):
+    """Four entries per row of 1536 columns: the single gathers run, the last one
+    with the dequantised output, against the oracle."""
+    from tests.dispatch_util import gather_cols_sparse
+    M, N, cols, t = 18, 4000, 1536, 4
+    assert gather_cols_sparse(levels, M, N, levels * cols, levels * t)
+    rng = np.random.default_rng(levels)
+    want = rng.integers(0, 2 ** 32, (M, N), dtype=np.uint32)
+    c, terms = to_dev_ring(want), []
+    for k in range(levels):
+        D = rng.integers(0, 2 ** 32, (M, cols + 3), dtype=np.uint32)
+        P = smp.sample_matrix("weight", N, cols, 8, 0x60 + k, 3, row_weight=t)
+        terms.append((m.mosaic_sparse_csr(m.rng(8, 0x60 + k, 3, m.DIST_WEIGHT, row_weight=t), N, cols),
+                      to_dev_ring(D)[:, 2: 2 + cols]))
+        want = ring_sub(want, ring_matmul(D[:, 2: 2 + cols], P.T))
+    sr, sc = torch.rand(M, device="cuda") * 1e-3, torch.rand(N, device="cuda") * 1e-3
+    y = torch.empty((M, N), device="cuda")
+    m.mosaic_sparse_gather_cols_terms(terms, M, c, subtract=True, y_f32=y, s_rows=sr, s_cols=sc)
+    assert np.array_equal(to_np_u32(c), want)
+    ref = (want.view(np.int32).astype(np.float32) * sr.cpu().numpy()[:, None]) * sc.cpu().numpy()[None, :]
+    assert np.array_equal(y.cpu().numpy(), ref)
