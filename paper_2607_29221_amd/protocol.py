@@ -186,6 +186,7 @@ class MaskedWeight:
                     m.mosaic_masked_matmul(f, prev, ri, K, rp, words)
                     m.mosaic_mask(None, words, None, ri, K, out_dig=same)
                     m.mosaic_mask(words, None, None, K, ri, out_dig=turned, x_transposed=True)
+                del Mi, NiT, f, words           # not held while the larger products below run
 
         # client: Lcat = [L | S_2 | ... | S_d] (sparse-only: L alone), and
         # S_{i+1} as compressed rows when the sparse form is kept

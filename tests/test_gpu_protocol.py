@@ -129,3 +129,21 @@ def test_unmask_form_by_token_count(monkeypatch, M, K, N, ranks):
     _check_run(A, W, p, SEED + 3 * M)
     expect_words = M <= 16 and N % 4 == 0
     assert calls == {"words": int(expect_words), "digits": int(not expect_words)}
+
+
+def test_init_w_holds_no_chain_operands():
+    """Depth 2, ranks 1536 and 1024: the largest product of Init W runs beside the
+    kept buffers, both chains in digits and its own output, not beside the
+    operands and the words of the chain's products (45 MB here)."""
+    from synthetic_inputs import PARAMS_PAPER_D2_SPARSE as P
+    K, N, R = 8192, 1024, sum(P.ranks)
+    W = torch.ones((N, K), dtype=torch.int8, device="cuda")
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    torch.cuda.reset_peak_memory_stats()
+    base = torch.cuda.memory_allocated()
+    w = gproto.MaskedWeight(W, P, 3, 1)
+    kept = torch.cuda.memory_allocated() - base
+    peak = torch.cuda.max_memory_allocated() - base
+    assert peak <= kept + 2 * 4 * K * R + 4 * N * K + (16 << 20), (peak, kept)
+    del w
