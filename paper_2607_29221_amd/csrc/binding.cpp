@@ -432,7 +432,9 @@ FUNCTION(cols_terms, 8) {
   NEED(matrix(a[2], M, N, at::kInt, false, &c) && matrix(a[4], M, N, at::kFloat, true, &f) &&
        vec(a[5], M, at::kFloat, !f.given(), &sr) && vec(a[6], N, at::kFloat, !f.given(), &sc) &&
        vec(a[7], N, at::kFloat, true, &bias) && truth(a[3], &subtract) && current_stream(&s));
-  if (mosaic::gather_cols_sparse((int)n, M, N, all_cols, all_entries))
+  // outputs that the last call would refuse are refused before the first has added anything
+  const bool outputs_ok = f.given() ? f.ld >= N : !bias.given();
+  if (outputs_ok && mosaic::gather_cols_sparse((int)n, M, N, all_cols, all_entries))
     return status([&] {
       for (Py_ssize_t l = 0; l < n; ++l) {
         const mosaic_sparse_term& t = terms[l];

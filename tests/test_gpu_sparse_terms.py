@@ -126,6 +126,11 @@ def test_gather_cols_terms_of_few_entries(levels):
                       to_dev_ring(D)[:, 2: 2 + cols]))
         want = ring_sub(want, ring_matmul(D[:, 2: 2 + cols], P.T))
     sr, sc = torch.rand(M, device="cuda") * 1e-3, torch.rand(N, device="cuda") * 1e-3
+    before = c.clone()
+    for bad in (dict(bias=sc), dict(y_f32=torch.empty((1, N), device="cuda").expand(M, N), s_rows=sr, s_cols=sc)):
+        with pytest.raises(m.MosaicError):       # refused before anything is added
+            m.mosaic_sparse_gather_cols_terms(terms, M, c, **bad)
+        assert torch.equal(c, before)
     y = torch.empty((M, N), device="cuda")
     m.mosaic_sparse_gather_cols_terms(terms, M, c, subtract=True, y_f32=y, s_rows=sr, s_cols=sc)
     assert np.array_equal(to_np_u32(c), want)
